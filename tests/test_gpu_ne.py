@@ -165,3 +165,35 @@ def test_normal_equations_errors(ms):
         with pytest.raises(ms.MsketchError) as e:
             ms.normal_equations_lstsq(to_dev(A2), to_dev(B2))
         assert e.value.code == ms.MS_ERR_UNSUPPORTED
+
+
+# Every tile-column count of the wide Gram pass (5 .. 17 columns of 16; the
+# tiles per wave and the rows of a slab differ between them), with the last
+# tile column full and with one column in it, at a row count that leaves a
+# partial slab (64, 32 and 16 rows) and at one slab or less.  R^T R is the Gram
+# matrix up to the Cholesky factorisation's backward error and the sum's
+# rounding: (n + 1) u + sqrt(d) u, below 5e-14 here; the bar is 1e-13.
+GRAM_CASES = ([(1000 + 7 * t, 16 * t - 1, 1) for t in range(5, 18)] +
+              [(1003 + t, 16 * t - 16, 1) for t in range(6, 18)] +
+              [(66, 65, 1), (129, 127, 2), (257, 256, 16)])
+
+
+@pytest.mark.parametrize("d,n,nrhs", GRAM_CASES)
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+def test_normal_equations_tile_columns(ms, d, n, nrhs, dtype):
+    print("normal_equations tiles d=%d n=%d nrhs=%d %s" % (d, n, nrhs, dtype), flush=True)
+    n = min(n, 256)
+    A, B = _problem(d, n, nrhs, 1.0, seed=d + n, dtype=dtype)
+    R = ms.empty_colmajor(n, n, torch.float64, "cuda")
+    X, _, ws = ms.normal_equations_lstsq(to_dev(A), to_dev(B), R=R)
+    ms.check_status(ws)
+    A64, B64 = A.astype(np.float64), B.astype(np.float64)
+    gram = A64.T @ A64
+    Rg = to_host(R)
+    assert np.all(np.tril(Rg, -1) == 0.0) and np.all(np.diag(Rg) > 0.0)
+    assert rel(Rg.T @ Rg, gram) <= 1e-13
+    # the normal equations' residual is small whatever kappa(A) is
+    Xh = to_host(X)
+    res = A64.T @ B64 - gram @ Xh
+    scale = np.linalg.norm(gram) * np.linalg.norm(Xh) + np.linalg.norm(A64.T @ B64)
+    assert np.linalg.norm(res) / scale <= 1e-13
