@@ -7,8 +7,9 @@
 // block and a second kernel adds the partials in a fixed order (four
 // consecutive runs of splits, each in split order, then the four run sums in
 // order), so the result does not depend on scheduling.  A 16-bit G uses
-// 256 x 144 output tiles staged through LDS; FP64 and FP32 use 64 x 64 tiles
-// with fragments loaded straight from memory.
+// 256 x 144 output tiles staged through LDS and an FP64 one 128-row tiles
+// likewise; FP32, and batched FP64 problems, use 64 x 64 tiles with fragments
+// loaded straight from memory.
 //
 // Matrix-core instructions (one 16x16 output block per instruction):
 //   FP64: v_mfma_f64_16x16x4_f64       (K step 4)
@@ -562,6 +563,173 @@ __global__ __launch_bounds__(256) void k_gemm_splitk(int M, int N, int64_t K,
                 tile / tiles_m);
 }
 
+// ------------------------------------------------------------ FP64 tiles
+// The FP64 stage: 128 x (16 NB) output tiles, eight waves, wave w owning the
+// 16 rows 16 w .. and all NB column blocks (8 NB accumulator registers, up to
+// 72), two waves a SIMD.  K advances in slabs of 32 staged in LDS (two
+// buffers, one barrier per slab, the next slab's loads in flight while the
+// current one is multiplied).  G's slab keeps its rows contiguous, one padded
+// row of 128 per k; Y's slab holds, per column block and group of 8 k, 64 slots
+// of 16 bytes (two consecutive k of one column), so that a staging write and a
+// fragment read are both contiguous.  Lane (i, q) = (l % 16, l / 16) takes k
+// = 2 q and 2 q + 1 of a group as its two products' k, in both operands.
+// Bound by the matrix cores for wide sketches (64 cycles per 16 x 16 x 4
+// product), by the latency of a few slabs for small ones.  Fragments loaded
+// straight from memory (64 x 64 tiles, each element fetched by every tile)
+// ran 512 x 131,072 . 131,072 x 257 in 1.80 ms; this takes 0.70 ms (49 TFLOP/s).
+constexpr int kDTM = 128, kDKS = 32, kDThreads = 512, kDMaxNB = 9;
+constexpr int kDRow = kDTM * 8 + 64;   // bytes of a padded k row of G: k rows 2 apart fall 32 banks apart
+
+template <int NB>
+constexpr int f64_buf_bytes() {
+  return kDKS * kDRow + kDKS * NB * 16 * 8;
+}
+
+template <int NB>
+__global__ __launch_bounds__(kDThreads, 2) void k_gemm_f64(int M, int N, int64_t K,
+                                                           const double *__restrict__ G,
+                                                           int64_t ldg,
+                                                           const double *__restrict__ Y,
+                                                           int64_t ldy,
+                                                           double *__restrict__ part,
+                                                           int64_t kchunk, int tiles_m, int tiles,
+                                                           int nsplit, int xcds) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  typedef double v2e __attribute__((ext_vector_type(2), aligned(8)));
+  typedef double v2d __attribute__((ext_vector_type(2)));
+  const int g = blockIdx.x;
+  const int x = g % xcds, jj = g / xcds;
+  const int split = x + xcds * (jj / tiles);
+  if (split >= nsplit) return;
+  const int tile = jj % tiles;
+  const int m0 = (tile % tiles_m) * kDTM, n0 = (tile / tiles_m) * (16 * NB);
+  const int64_t kb = (int64_t)split * kchunk, ke = min(K, kb + kchunk);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, lk = lane >> 4;
+
+  // staging: G tasks q (k = tid / 64 + 8 q of the slab, rows 2 (tid % 64) and
+  // the next one), Y tasks q (slot tid + 512 q).  A row pair past M reads the
+  // last pair and a column past N the last column: their products are not
+  // stored (M odd: the last row sits second in the pair read for it).
+  constexpr int QY = (NB * 256 + kDThreads - 1) / kDThreads;
+  v2d ga[4], ya[QY];
+  const int grow = m0 + 2 * lane;
+  const bool lastrow = grow == M - 1;
+  const double *gp = G + max(0, min(grow, M - 2)) + (kb + wave) * ldg;
+  const double *yp[QY];
+  const int yk = 8 * ((tid >> 6) & 3) + 2 * ((tid >> 4) & 3);   // k within the slab
+#pragma unroll
+  for (int q = 0; q < QY; ++q) {
+    const int blk = min((tid >> 8) + 2 * q, NB - 1);
+    yp[q] = Y + (int64_t)min(n0 + 16 * blk + (tid & 15), N - 1) * ldy + kb + yk;
+  }
+  auto at2 = [&](const double *p) {
+    const v2e t = *(const __attribute__((address_space(1))) v2e *)p;
+    return v2d{t[0], t[1]};
+  };
+  auto fetch = [&](int64_t ko) {   // the whole slab at k offset ko (from kb)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) ga[q] = at2(gp + (ko + 8 * q) * ldg);
+#pragma unroll
+    for (int q = 0; q < QY; ++q) ya[q] = at2(yp[q] + ko);
+  };
+  auto fetch_part = [&](int64_t ko) {   // its k past ke zero in both operands, every load guarded
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int64_t k = kb + ko + wave + 8 * q;
+      ga[q] = v2d{0.0, 0.0};
+      if (k < ke) {
+        if (grow < M) ga[q][lastrow] = gload(G + grow + k * ldg);
+        if (grow + 1 < M) ga[q][1] = gload(G + grow + 1 + k * ldg);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < QY; ++q) {
+      const int64_t k = kb + ko + yk;
+      ya[q] = v2d{0.0, 0.0};
+      if (k < ke) ya[q][0] = gload(yp[q] + ko);
+      if (k + 1 < ke) ya[q][1] = gload(yp[q] + ko + 1);
+    }
+  };
+  auto put = [&](unsigned char *buf) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      *reinterpret_cast<v2d *>(buf + (wave + 8 * q) * kDRow + lane * 16) =
+          lastrow ? v2d{ga[q][1], 0.0} : ga[q];
+#pragma unroll
+    for (int q = 0; q < QY; ++q)
+      if ((tid >> 8) + 2 * q < NB)
+        *reinterpret_cast<v2d *>(buf + kDKS * kDRow + (tid + kDThreads * q) * 16) = ya[q];
+  };
+
+  v4d acc[NB];
+#pragma unroll
+  for (int j = 0; j < NB; ++j) acc[j] = v4d{0.0, 0.0, 0.0, 0.0};
+  const bool active = m0 + 16 * wave < M;   // this wave's rows exist (uniform)
+  constexpr int bufsz = f64_buf_bytes<NB>();
+  const int64_t klen = ke - kb;
+  auto products = [&](const unsigned char *buf) {
+    const unsigned char *pa = buf + 2 * lk * kDRow + (16 * wave + li) * 8;
+    const unsigned char *pb = buf + kDKS * kDRow + lane * 16;
+    double a0, a1, na0, na1;
+    v2d b[NB], nb[NB];
+    auto frags = [&](int h, double &f0, double &f1, v2d (&fb)[NB]) {
+      f0 = *reinterpret_cast<const double *>(pa + 8 * h * kDRow);
+      f1 = *reinterpret_cast<const double *>(pa + (8 * h + 1) * kDRow);
+#pragma unroll
+      for (int j = 0; j < NB; ++j) fb[j] = *reinterpret_cast<const v2d *>(pb + (4 * j + h) * 1024);
+    };
+    frags(0, a0, a1, b);
+#pragma unroll
+    for (int h = 0; h < kDKS / 8; ++h) {
+      if (h + 1 < kDKS / 8) frags(h + 1, na0, na1, nb);
+      __builtin_amdgcn_sched_barrier(0);   // the next group's reads before this one's products
+#pragma unroll
+      for (int j = 0; j < NB; ++j) acc[j] = Mf<DT_F64>::mma(a0, b[j][0], acc[j]);
+#pragma unroll
+      for (int j = 0; j < NB; ++j) acc[j] = Mf<DT_F64>::mma(a1, b[j][1], acc[j]);
+      a0 = na0;
+      a1 = na1;
+#pragma unroll
+      for (int j = 0; j < NB; ++j) b[j] = nb[j];
+    }
+  };
+  // whole slabs, then the part of one that may be left (M = 1: every slab)
+  const int64_t whole = M >= 2 ? klen / kDKS * kDKS : 0;
+  int cur = 0;
+  if (whole > 0) {
+    fetch(0);
+    put(smem_raw);
+  }
+  __syncthreads();
+  for (int64_t ko = 0; ko < whole; ko += kDKS) {
+    // (past the last one the same slab again, which is not used)
+    fetch(min(ko + kDKS, whole - kDKS));
+    if (active) products(smem_raw + cur * bufsz);
+    put(smem_raw + (cur ^ 1) * bufsz);
+    __syncthreads();
+    cur ^= 1;
+  }
+  for (int64_t ko = whole; ko < klen; ko += kDKS) {
+    fetch_part(ko);
+    put(smem_raw);
+    __syncthreads();
+    if (active) products(smem_raw);
+    __syncthreads();
+  }
+  double *P = part + (int64_t)split * M * N;
+#pragma unroll
+  for (int j = 0; j < NB; ++j) {
+    const int col = n0 + 16 * j + li;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = m0 + 16 * wave + lk + 4 * r;
+      if (row < M && col < N) P[row + (int64_t)col * M] = acc[j][r];
+    }
+  }
+}
+
 // FP16 column scales: cs[2c] = 2^-e_c and cs[2c + 1] = 2^e_c with
 // e_c = floor(log2 max_k |Y[k, c]|) - 14, so the scaled column's largest
 // magnitude lies in [2^14, 2^15) (FP16's largest finite value is 65504).
@@ -796,18 +964,38 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, ms_dtype g_dtype) {
   p.M = (int)M;
   p.N = (int)N;
   p.K = K;
-  const bool h16 = g_dtype == MS_BF16 || g_dtype == MS_F16;
+  const bool h16 = g_dtype == MS_BF16 || g_dtype == MS_F16, f64 = g_dtype == MS_F64;
   // 16-bit G: 256 x 144 tiles, about one workgroup per compute unit, at
   // least 512 K values per workgroup (so the partials stay small next to the
-  // chunk of G and Y each workgroup reads); else 64 x 64 tiles, ~1024
-  // workgroups, at least 128 K values each
-  p.tiles_m = (int)(h16 ? (M + kWTM - 1) / kWTM : (M + 63) / 64);
+  // chunk of G and Y each workgroup reads).  FP32: 64 x 64 tiles, ~1024
+  // workgroups, at least 128 K values each.
+  const int64_t target = h16 || f64 ? 256 : 1024, kmin = h16 ? 512 : 128;
+  const int64_t ks = h16 ? kWKS : f64 ? kDKS : 4;
+  const int64_t kmax = (K + kmin - 1) / kmin;   // splits of at least kmin K values
+  p.tiles_m = (int)(h16 ? (M + kWTM - 1) / kWTM : f64 ? (M + kDTM - 1) / kDTM : (M + 63) / 64);
   p.tiles_n = (int)(h16 ? (N + kWTN - 1) / kWTN : (N + 63) / 64);
-  const int64_t ks = h16 ? kWKS : 4;
-  const int64_t tiles = (int64_t)p.tiles_m * p.tiles_n;
-  const int64_t target = h16 ? 256 : 1024, kmin = h16 ? 512 : 128;
-  int64_t ns = std::max<int64_t>(1, std::min<int64_t>((target + tiles - 1) / tiles,
-                                                      (K + kmin - 1) / kmin));
+  int64_t ns;
+  if (f64) {
+    // FP64: 128 x (16 NB) tiles, at most one workgroup per compute unit, at
+    // least 128 K values each.  Where the sketch alone fits
+    // sketch_lstsq_noalloc's scratch array, no more partials than
+    // ceil(1024 / (64 x 64 tiles)) splits make: its limit is stated with them.
+    // If the splits leave compute units idle, the column blocks go to more,
+    // narrower tiles (128 x 8192 . 8192 x 65, 64 splits: one 80-column tile
+    // 20.6 us on 64 compute units, three 32-column tiles 12.8 us).
+    const int64_t t64 = std::max<int64_t>(1, ((M + 63) / 64) * ((N + 63) / 64));
+    int64_t cap = kmax;
+    if (K * N * 8 <= MS_NOALLOC_SCRATCH_BYTES) cap = std::min(cap, (1024 + t64 - 1) / t64);
+    const int64_t nblk = std::max<int64_t>(1, (N + 15) / 16), tm = std::max(1, p.tiles_m);
+    const int64_t tn = std::max((nblk + kDMaxNB - 1) / kDMaxNB,
+                                std::min(nblk, target / (tm * std::max<int64_t>(1, cap))));
+    p.nb = (int)((nblk + tn - 1) / tn);
+    p.tiles_n = (int)((nblk + p.nb - 1) / p.nb);
+    ns = std::max<int64_t>(1, std::min(cap, target / (tm * p.tiles_n)));
+  } else {
+    const int64_t tiles = std::max<int64_t>(1, (int64_t)p.tiles_m * p.tiles_n);
+    ns = std::max<int64_t>(1, std::min<int64_t>((target + tiles - 1) / tiles, kmax));
+  }
   ns = std::min<int64_t>(ns, 65535);
   int64_t kc = (K + ns - 1) / ns;
   kc = (kc + ks - 1) / ks * ks;
@@ -864,14 +1052,29 @@ hipError_t launch_gemm(const GemmPlan &p, ms_dtype g_dtype, const void *G, int64
   const dim3 grid((unsigned)((int64_t)xcds * tiles * ((p.nsplit + xcds - 1) / xcds)));
   const bool reduce = Z != nullptr || z64 != nullptr;  // otherwise the caller consumes the partials
   switch (g_dtype) {
-    case MS_F64:
-      hipLaunchKernelGGL(k_gemm_splitk<DT_F64>, grid, dim3(256), 0, st, p.M, p.N, p.K,
-                         (const double *)G, ldg, (const double *)Y, ldy, (double *)partials,
-                         p.kchunk, p.tiles_m, tiles, p.nsplit, xcds);
+    case MS_F64: {
+      hipError_t e = hipErrorInvalidValue;
+      switch (p.nb) {
+#define MS_F64_NB(NB_)                                                                          \
+  case NB_: {                                                                                   \
+    constexpr int lds = 2 * f64_buf_bytes<NB_>();                                               \
+    e = allow_dynamic_lds((const void *)k_gemm_f64<NB_>, lds);                                  \
+    if (e != hipSuccess) return e;                                                              \
+    hipLaunchKernelGGL(k_gemm_f64<NB_>, grid, dim3(kDThreads), lds, st, p.M, p.N, p.K,          \
+                       (const double *)G, ldg, (const double *)Y, ldy, (double *)partials,      \
+                       p.kchunk, p.tiles_m, tiles, p.nsplit, xcds);                             \
+    break;                                                                                      \
+  }
+        MS_F64_NB(1) MS_F64_NB(2) MS_F64_NB(3) MS_F64_NB(4) MS_F64_NB(5) MS_F64_NB(6)
+        MS_F64_NB(7) MS_F64_NB(8) MS_F64_NB(9)
+#undef MS_F64_NB
+      }
+      if (e != hipSuccess) return e;
       if (reduce)
         hipLaunchKernelGGL((k_reduce_splits<double, double>), dim3(rblocks), dim3(256), 0, st, p.M,
                            p.N, p.nsplit, (const double *)partials, (double *)Z, ldz, z64);
       break;
+    }
     case MS_F32:
       hipLaunchKernelGGL(k_gemm_splitk<DT_F32>, grid, dim3(256), 0, st, p.M, p.N, p.K,
                          (const float *)G, ldg, (const float *)Y, ldy, (float *)partials,

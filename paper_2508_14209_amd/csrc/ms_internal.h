@@ -147,6 +147,7 @@ struct GemmPlan {
   int M, N;
   int64_t K;
   int tiles_m, tiles_n, nsplit;
+  int nb;  // FP64: 16-column blocks per tile
   int64_t kchunk;
   size_t partial_bytes;  // workspace for the split-K partials
   size_t ybf16_bytes;    // workspace for the BF16 copy of Y (BF16 path)

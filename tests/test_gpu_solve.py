@@ -67,6 +67,33 @@ def test_gaussian_stage_bf16_full_width_sampled(ms, orc):
     assert rel(to_host(Z)[:, cols], Zr) <= 1e-5
 
 
+# The FP64 tile (128 rows, 16 to 144 columns, slabs of 32 k): one row and
+# two, odd and even row counts around the tile, every count of column blocks,
+# K below, at and past a slab, and column starts that are not 16-byte aligned
+# (odd leading dimensions).  Bar: both sums obey Higham's bound, so entry by
+# entry they differ by at most 2 (K + splits) u |G| |Y|.
+@pytest.mark.parametrize("k2,k,nc,pad", [
+    (1, 33, 1, 0), (2, 1, 16, 1), (3, 31, 17, 1), (15, 32, 33, 0), (16, 64, 48, 3),
+    (127, 65, 49, 1), (128, 4097, 80, 0), (129, 1000, 81, 1), (130, 2048, 112, 5),
+    (255, 129, 113, 0), (256, 8191, 128, 1), (257, 300, 129, 0), (384, 512, 144, 0),
+    (64, 640, 160, 1), (500, 96, 257, 0), (40, 70000, 100, 0)])
+def test_gaussian_f64_tiles(ms, k2, k, nc, pad):
+    print("gaussian f64 tile k2=%d k=%d nc=%d pad=%d" % (k2, k, nc, pad), flush=True)
+    rng = np.random.default_rng(k2 + k + nc)
+    G, Y = rng.standard_normal((k2, k)), rng.standard_normal((k, nc))
+
+    def dev(a):
+        t = torch.full((a.shape[1], a.shape[0] + pad), float("nan"), dtype=torch.float64,
+                       device="cuda")
+        t[:, :a.shape[0]] = torch.from_numpy(np.ascontiguousarray(a.T)).cuda()
+        return t.t()[:a.shape[0]]
+
+    Z, ws = ms.gaussian_apply(dev(G), dev(Y))
+    ms.check_status(ws)
+    err = np.abs(to_host(Z) - G @ Y)
+    assert np.all(err <= 2 * (k + 256) * 2.0 ** -53 * (np.abs(G) @ np.abs(Y)))
+
+
 def test_gaussian_identity_exact(ms):
     # G = I (k2 = k): Z = Y bit for bit in FP64
     k, nc = 64, 5
