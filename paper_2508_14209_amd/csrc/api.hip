@@ -286,8 +286,9 @@ hipError_t run_countsketch(int64_t d, int64_t k, const Cols<T> &c, const int32_t
   hipError_t e;
   if (mode == MS_CS_SORTED && L.bkeys_bytes) {
     e = launch_zero_status(status, st);
-    if (e == hipSuccess) e = launch_bf_keys(d, k, h, s, at<uint32_t>(ws, L.bkeys), status, st);
-    if (e == hipSuccess) e = launch_bf_fold<T>(d, k, c, at<uint32_t>(ws, L.bkeys), Y, ldy, st);
+    const bool sl = cs_blockfold_sliced(d, k, c.ncols);
+    if (e == hipSuccess) e = launch_bf_keys(d, k, h, s, at<uint32_t>(ws, L.bkeys), sl, status, st);
+    if (e == hipSuccess) e = launch_bf_fold<T>(d, k, c, at<uint32_t>(ws, L.bkeys), sl, Y, ldy, st);
     return e;
   }
   if (mode == MS_CS_SORTED) {
@@ -682,8 +683,8 @@ ms_status sketch_lstsq(int64_t d, int64_t n, int64_t nrhs, int64_t k, int64_t k2
     if (e != hipSuccess) break;
     Cols<double> cr{r, d, nullptr, 0, (int)nrhs, (int)nrhs};
     if (mode == MS_CS_SORTED && L.cs.bkeys_bytes)
-      e = launch_bf_fold<double>(d, k, cr, at<uint32_t>(ws, L.cs.bkeys), at<double>(ws, L.yr), k,
-                                 st);
+      e = launch_bf_fold<double>(d, k, cr, at<uint32_t>(ws, L.cs.bkeys),
+                                 cs_blockfold_sliced(d, k, nc), at<double>(ws, L.yr), k, st);
     else if (mode == MS_CS_SORTED)
       e = launch_cs_sorted_cols<double>(k, cr, at<int32_t>(ws, L.cs.off), at<uint32_t>(ws, L.cs.sperm),
                                    at<double>(ws, L.yr), k, st);

@@ -16,6 +16,11 @@
 // bucket's sum.  Per bucket the additions therefore happen in ascending row
 // order over the whole column -- the order of the sequential loop -- while A
 // is read in its stored order instead of gathered in bucket order.
+//
+// Where a thread can own whole buckets (32 to 16384 buckets, up to about 128
+// columns) the sorted rows are stored as 16-bit entries grouped by fold thread,
+// and every thread walks the entries of its own buckets with their sums in
+// registers (k_bf_fold_sliced).
 #include <algorithm>
 
 #include "ms_internal.h"
@@ -25,6 +30,7 @@ namespace ms {
 namespace {
 
 typedef uint32_t bf_u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t bf_u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kBfRows = 4096;               // rows per block (12 bits of the key)
 constexpr int kBfT = 1024;                  // threads
@@ -99,8 +105,20 @@ __global__ __launch_bounds__(kBfT) void k_bf_keys(int64_t d, int k, const int32_
 constexpr int kBfCountMaxK = 16384;
 constexpr int kBfCountMaxRun = 64;
 
+// Sliced keys (cs_blockfold_sliced): the buckets in at most 4096
+// slices of B consecutive buckets (B a power of two up to 4), each folded by
+// one thread.  A block is stored, in the 16 KB its 32-bit keys would take, as
+// 4096 16-bit entries in (bucket, row) order -- bucket within its slice |
+// row << 3 | sign << 15 -- followed by the slices' end positions (16 bits each).
+constexpr int kBfSlices = 4096;
+constexpr int kBfSliceMinK = 32;
+constexpr int bf_slice_buckets(int64_t k) {
+  return k <= kBfSlices ? 1 : k <= 2 * kBfSlices ? 2 : 4;
+}
+
 size_t bf_count_lds(int64_t k) { return (size_t)(k + 1 + 3) / 4 * 16 + (size_t)kBfRows * 4; }
 
+template <bool SLICED>
 __global__ __launch_bounds__(kBfT) void k_bf_keys_count(int64_t d, int k,
                                                         const int32_t *__restrict__ h,
                                                         const int8_t *__restrict__ s,
@@ -143,10 +161,24 @@ __global__ __launch_bounds__(kBfT) void k_bf_keys_count(int64_t d, int k,
   if (lane == 63) wsum[w] = incl;
   __syncthreads();
   const bool longrun = s_long != 0;
-  if (longrun) {
+  // thread t's sorted keys 4t .. 4t + 3, as keys or as 16-bit entries
+  const int nb = SLICED ? bf_slice_buckets(k) : 1;
+  auto store = [&]() {
+    if (SLICED) {
+      uint32_t e[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        e[q] = (bf_bucket(v[q]) & (uint32_t)(nb - 1)) | (v[q] & 0xfffu) << 3 | (v[q] >> 31) << 15;
+      *reinterpret_cast<uint2 *>(keys + r0 + 2 * tid) = make_uint2(e[0] | e[1] << 16, e[2] | e[3] << 16);
+    } else {
+      *reinterpret_cast<uint4 *>(keys + r0 + 4 * tid) = make_uint4(v[0], v[1], v[2], v[3]);
+    }
+  };
+  uint16_t *ends = reinterpret_cast<uint16_t *>(keys + r0 + kBfRows / 2);
+  if (longrun && !SLICED) {
     // a bucket too long for the insertion sort: the network
     sort4096_regs(v, key);
-    *reinterpret_cast<uint4 *>(keys + r0 + 4 * tid) = make_uint4(v[0], v[1], v[2], v[3]);
+    store();
     return;
   }
   uint32_t run = incl - loc;
@@ -160,6 +192,16 @@ __global__ __launch_bounds__(kBfT) void k_bf_keys_count(int64_t d, int k,
     }
   }
   __syncthreads();
+  if (SLICED) {
+    // a slice ends where the next one's first bucket starts (cnt[k]: the padding)
+    for (int sl = tid; sl * nb < k; sl += kBfT) ends[sl] = (uint16_t)cnt[min((sl + 1) * nb, k)];
+    if (longrun) {
+      sort4096_regs(v, key);
+      store();
+      return;
+    }
+    __syncthreads();   // cnt is advanced below
+  }
 #pragma unroll
   for (int e = 0; e < 4; ++e) key[atomicAdd(&cnt[bucket_of(v[e])], 1u)] = v[e];
   __syncthreads();
@@ -177,7 +219,12 @@ __global__ __launch_bounds__(kBfT) void k_bf_keys_count(int64_t d, int k,
     }
   }
   __syncthreads();
-  *reinterpret_cast<uint4 *>(keys + r0 + 4 * tid) = *reinterpret_cast<const uint4 *>(key + 4 * tid);
+  const uint4 sorted = *reinterpret_cast<const uint4 *>(key + 4 * tid);
+  v[0] = sorted.x;
+  v[1] = sorted.y;
+  v[2] = sorted.z;
+  v[3] = sorted.w;
+  store();
 }
 
 template <typename T>
@@ -335,6 +382,158 @@ __global__ __launch_bounds__(kBfT) void k_bf_fold(int64_t d, int k, Cols<T> cols
   for (uint32_t i = tid; i < m1 - m0; i += kBfT) Y[(m0 + i) + (int64_t)c * ldy] = acc[i];
 }
 
+// The fold of sliced keys: workgroup (column c, part p) -- the parts of a column
+// on one die, whose L2 fetches the column once -- owns slices [s0, s1) of column
+// c, thread t the slices s0 + t + 1024 n (n < NS) with their B sums each
+// in registers.  The column's 4096 values of a block and its entries are
+// staged in LDS (two buffers, one barrier per block, loads in flight kSlAhead
+// blocks ahead); a thread then walks its entries, gathering each one's value
+// from LDS while the entry after it is read.
+// Bound by what one compute unit reads from its L2 (every part reads the whole
+// column, about 30 bytes a cycle: 1.0 of the 1.4 ms below) and then by the walk,
+// in which a wave takes as many steps as the longest of its 64 slices (4 to 5
+// where they average one).  4,194,304 x 65 FP64, k = 8192: 1.37 ms against 2.06
+// for bf_fold_column, whose threads own positions instead (every thread
+// looks at every position of its four, reads and writes the sums in LDS).
+constexpr int kSlAhead = 4;
+
+template <typename T, int B, int NS>
+__global__ __launch_bounds__(kBfT) void k_bf_fold_sliced(int64_t d, int k, Cols<T> cols, int parts,
+                                                         int xcds,
+                                                         const uint32_t *__restrict__ keys,
+                                                         T *__restrict__ Y, int64_t ldy) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  // (the entries first: the one past a buffer's end is read, not used)
+  uint16_t *lent = reinterpret_cast<uint16_t *>(smem_raw);   // 2 kBfRows
+  T *stage = reinterpret_cast<T *>(lent + 2 * kBfRows);      // 2 kBfRows
+  // thread t stages 16 bytes of values kV times, kBfT threads apart (contiguous
+  // across a wave, in memory and in LDS)
+  constexpr int kR = 16 / (int)sizeof(T), kV = kBfRows / kBfT / kR;
+  typedef T V __attribute__((ext_vector_type(kR)));
+  typedef T Va __attribute__((ext_vector_type(kR), aligned(sizeof(T))));
+  const int tid = threadIdx.x;
+  const int x = blockIdx.x % xcds, j0 = blockIdx.x / xcds;
+  const int part = j0 % parts, c = (j0 / parts) * xcds + x;
+  if (c >= cols.ncols) return;
+  const int nsl = (k + B - 1) / B;
+  const int s0 = (int)((int64_t)nsl * part / parts), s1 = (int)((int64_t)nsl * (part + 1) / parts);
+  const T *col = bf_col(cols, c);
+  const int nblk = (int)((d + kBfRows - 1) / kBfRows);
+  T acc[NS][B];
+  int sl[NS];
+#pragma unroll
+  for (int n = 0; n < NS; ++n) {
+    sl[n] = min(s0 + tid + kBfT * n, s1 - 1);   // past s1: the last slice again, not stored
+#pragma unroll
+    for (int q = 0; q < B; ++q) acc[n][q] = T(0);
+  }
+  // a last block that is not whole is staged with the rows before it (the
+  // last 4096 of the column), its row 0 at position `shift`: every load is
+  // unconditional, so that the loads in flight can be counted exactly
+  const int shift = (int)((int64_t)nblk * kBfRows - d);
+  V v[kSlAhead][kV];
+  bf_u32x2 ev[kSlAhead];
+  uint16_t lo[kSlAhead][NS], hi[kSlAhead][NS];   // the slices' starts and ends, as loaded
+  // the next block to fetch (past the last one: the last one again, not
+  // used), uniform pointers advanced block by block
+  const T *cb = nblk > 1 ? col : col + (d - kBfRows);
+  const uint32_t *kb = keys;
+  int fb = 0;
+  auto fetch = [&](int j) {
+#pragma unroll
+    for (int q = 0; q < kV; ++q)
+      v[j][q] = *(const __attribute__((address_space(1))) Va *)(cb + kR * (tid + kBfT * q));
+    ev[j] = gload(reinterpret_cast<const bf_u32x2 *>(kb) + tid);
+    const uint16_t *ends = reinterpret_cast<const uint16_t *>(kb + kBfRows / 2);
+#pragma unroll
+    for (int n = 0; n < NS; ++n) {
+      lo[j][n] = gload(ends + max(sl[n] - 1, 0));
+      hi[j][n] = gload(ends + sl[n]);
+    }
+    ++fb;
+    cb = fb < nblk - 1 ? cb + kBfRows : col + (d - kBfRows);
+    kb += fb < nblk ? kBfRows : 0;
+  };
+  auto put = [&](int j, int buf) {
+#pragma unroll
+    for (int q = 0; q < kV; ++q)
+      *reinterpret_cast<V *>(stage + buf * kBfRows + kR * (tid + kBfT * q)) = v[j][q];
+    *reinterpret_cast<bf_u32x2 *>(lent + buf * kBfRows + 4 * tid) = ev[j];
+  };
+  uint16_t cl[NS], ch[NS];
+  auto fold = [&](const T *sg, const uint16_t *le) {
+    const unsigned char *sb = reinterpret_cast<const unsigned char *>(sg);
+    const unsigned char *eb = reinterpret_cast<const unsigned char *>(le);
+#pragma unroll
+    for (int n = 0; n < NS; ++n) {
+      uint32_t p = sl[n] > 0 ? 2u * cl[n] : 0u;
+      const uint32_t pe = 2u * ch[n];
+      if (p < pe) {
+        int e = *reinterpret_cast<const int16_t *>(eb + p);
+        do {
+          // this entry's value and the next entry (at the end: one not used)
+          // are read together; the empty statement keeps the compiler from
+          // moving the second read into the next turn, behind its use
+          const uint32_t at = sizeof(T) == 8 ? (e & 0x7ff8) : ((e >> 1) & 0x3ffc);
+          T xv = *reinterpret_cast<const T *>(sb + at);
+          p += 2;
+          int en = *reinterpret_cast<const int16_t *>(eb + p);
+          asm volatile("" : "+v"(xv), "+v"(en));
+          xv = apply_sign(xv, (uint32_t)e);
+          // (adding +0.0 to the others keeps every bit: a sum from +0.0 is
+          // never -0.0)
+#pragma unroll
+          for (int m = 0; m < B; ++m)
+            acc[n][m] = acc[n][m] + (B == 1 || (e & (B - 1)) == m ? xv : T(0));
+          e = en;
+        } while (p < pe);
+      }
+    }
+  };
+#pragma unroll
+  for (int j = 0; j < kSlAhead; ++j) fetch(j);
+  put(0, 0);
+#pragma unroll
+  for (int n = 0; n < NS; ++n) {
+    cl[n] = lo[0][n];
+    ch[n] = hi[0][n];
+  }
+  fetch(0);
+  __syncthreads();
+  static_assert(kSlAhead % 2 == 0, "the staging buffer of block b0 + j is j % 2");
+  for (int b0 = 0; b0 < nblk; b0 += kSlAhead) {
+#pragma unroll
+    for (int j = 0; j < kSlAhead; ++j) {
+      if (b0 + j >= nblk) break;
+      constexpr int kNext[kSlAhead] = {1, 2, 3, 0};
+      const int jn = kNext[j], cur = j & 1;
+      uint16_t nl[NS], nh[NS];
+      put(jn, cur ^ 1);   // (after the last block: a block that is not folded)
+#pragma unroll
+      for (int n = 0; n < NS; ++n) {
+        nl[n] = lo[jn][n];
+        nh[n] = hi[jn][n];
+      }
+      fetch(jn);
+      fold(stage + cur * kBfRows + (b0 + j + 1 < nblk ? 0 : shift), lent + cur * kBfRows);
+#pragma unroll
+      for (int n = 0; n < NS; ++n) {
+        cl[n] = nl[n];
+        ch[n] = nh[n];
+      }
+      __syncthreads();   // this block folded, the next one staged
+    }
+  }
+#pragma unroll
+  for (int n = 0; n < NS; ++n)
+    if (s0 + tid + kBfT * n < s1)
+#pragma unroll
+      for (int q = 0; q < B; ++q) {
+        const int m = sl[n] * B + q;
+        if (m < k) Y[m + (int64_t)c * ldy] = acc[n][q];
+      }
+}
+
 // ------------------------------------------------------------------ batched
 
 // Persistent over every problem's key blocks: problem p's block b sorted
@@ -453,16 +652,44 @@ size_t cs_blockfold_key_bytes(int64_t d) {
   return align_up((size_t)nblk * kBfRows * 4);
 }
 
+namespace {
+
+// Parts of a column in the fold of sliced keys (each reads all of it): as many
+// as the compute units of the column's die hold at one workgroup each.
+int bf_sliced_parts(int ncols) {
+  const DevInfo &di = dev_info();
+  const int xcds = std::max(1, di.xcds), per = std::max(1, (ncols + xcds - 1) / xcds);
+  return std::max(1, std::min(16, di.cus / xcds / per));
+}
+
+}  // namespace
+
+// Sliced keys are used where a fold thread then owns at most two slices (up
+// to 128 columns, and more for few buckets): 4,194,304 x 65 FP64, k = 8192:
+// 1.40 ms against 2.08 for positions; with four slices a thread (129 columns,
+// k = 8192) 3.3 against 2.4.  Fewer than 32 buckets (chains of more than 128
+// rows a block) keep the keys too.
+bool cs_blockfold_sliced(int64_t d, int64_t k, int64_t ncols) {
+  if (d < kBfRows || k < kBfSliceMinK || k > kBfCountMaxK || ncols < 1 || ncols > 65535) return false;
+  const int64_t B = bf_slice_buckets(k), nsl = (k + B - 1) / B, parts = bf_sliced_parts((int)ncols);
+  return (nsl + parts - 1) / parts <= 2 * kBfT;
+}
+
 hipError_t launch_bf_keys(int64_t d, int64_t k, const int32_t *h, const int8_t *s, uint32_t *keys,
-                          int *status, hipStream_t st) {
-  if (d < 1 || k < 1 || k > kBfMaxK) return hipErrorInvalidValue;
+                          bool sliced, int *status, hipStream_t st) {
+  if (d < 1 || k < 1 || k > kBfMaxK || (sliced && k > kBfCountMaxK)) return hipErrorInvalidValue;
   const int64_t nblk = (d + kBfRows - 1) / kBfRows;
   if (k <= kBfCountMaxK) {
     const size_t lds = bf_count_lds(k);
-    hipError_t e = allow_dynamic_lds((const void *)k_bf_keys_count, (int)lds);
+    hipError_t e = allow_dynamic_lds(sliced ? (const void *)k_bf_keys_count<true>
+                                            : (const void *)k_bf_keys_count<false>, (int)lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_bf_keys_count, dim3((unsigned)nblk), dim3(kBfT), lds, st, d, (int)k, h, s,
-                       keys, status);
+    if (sliced)
+      hipLaunchKernelGGL(k_bf_keys_count<true>, dim3((unsigned)nblk), dim3(kBfT), lds, st, d,
+                         (int)k, h, s, keys, status);
+    else
+      hipLaunchKernelGGL(k_bf_keys_count<false>, dim3((unsigned)nblk), dim3(kBfT), lds, st, d,
+                         (int)k, h, s, keys, status);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(k_bf_keys, dim3((unsigned)nblk), dim3(kBfT), 0, st, d, (int)k, h, s, keys,
@@ -470,9 +697,36 @@ hipError_t launch_bf_keys(int64_t d, int64_t k, const int32_t *h, const int8_t *
   return hipGetLastError();
 }
 
+template <typename T, int B, int NS>
+static hipError_t launch_bf_sliced(int64_t d, int64_t k, const Cols<T> &c, int parts,
+                                   const uint32_t *keys, T *Y, int64_t ldy, hipStream_t st) {
+  constexpr size_t lds = (size_t)2 * kBfRows * (sizeof(T) + 2);
+  hipError_t e = allow_dynamic_lds((const void *)k_bf_fold_sliced<T, B, NS>, (int)lds);
+  if (e != hipSuccess) return e;
+  const int xcds = std::max(1, dev_info().xcds);
+  hipLaunchKernelGGL((k_bf_fold_sliced<T, B, NS>),
+                     dim3((unsigned)((c.ncols + xcds - 1) / xcds * xcds * parts)), dim3(kBfT), lds,
+                     st, d, (int)k, c, parts, xcds, keys, Y, ldy);
+  return hipGetLastError();
+}
+
 template <typename T>
-hipError_t launch_bf_fold(int64_t d, int64_t k, const Cols<T> &c, const uint32_t *keys, T *Y,
-                          int64_t ldy, hipStream_t st) {
+hipError_t launch_bf_fold(int64_t d, int64_t k, const Cols<T> &c, const uint32_t *keys,
+                          bool sliced, T *Y, int64_t ldy, hipStream_t st) {
+  if (sliced) {
+    // (the residuals' fold has fewer columns than the keys were chosen for)
+    if (!cs_blockfold_sliced(d, k, c.ncols)) return hipErrorInvalidValue;
+    const int B = bf_slice_buckets(k);
+    const int nsl = (int)((k + B - 1) / B);
+    const int parts = std::min(bf_sliced_parts(c.ncols), nsl);
+    const bool one = (nsl + parts - 1) / parts <= kBfT;   // slices per thread: 1 or 2
+#define MS_SLICED(B_)                                                                          \
+  if (B == B_)                                                                                 \
+    return one ? launch_bf_sliced<T, B_, 1>(d, k, c, parts, keys, Y, ldy, st)                  \
+               : launch_bf_sliced<T, B_, 2>(d, k, c, parts, keys, Y, ldy, st);
+    MS_SLICED(1) MS_SLICED(2) MS_SLICED(4)
+#undef MS_SLICED
+  }
   const BfShape sh = bf_shape(k, c.ncols, sizeof(T));
   if (!sh.parts) return hipErrorInvalidValue;
   // two staging buffers when they leave the same workgroup count
@@ -528,8 +782,8 @@ template hipError_t launch_batch_bf_fold<double, 1>(int, const ms_problem *, con
                                                     hipStream_t);
 
 template hipError_t launch_bf_fold<double>(int64_t, int64_t, const Cols<double> &,
-                                           const uint32_t *, double *, int64_t, hipStream_t);
+                                           const uint32_t *, bool, double *, int64_t, hipStream_t);
 template hipError_t launch_bf_fold<float>(int64_t, int64_t, const Cols<float> &, const uint32_t *,
-                                          float *, int64_t, hipStream_t);
+                                          bool, float *, int64_t, hipStream_t);
 
 }  // namespace ms

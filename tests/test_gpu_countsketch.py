@@ -269,3 +269,49 @@ def test_range_errors_reported(ms, mode):
     with pytest.raises(ms.MsketchError) as e:
         ms.check_status(ws)
     assert e.value.code == ms.MS_ERR_RANGE
+
+
+# The deterministic fold by slices of buckets (one fold thread per slice): d at
+# and around a 4096-row block (below one block the other form runs), bucket
+# counts at the edges of the slice widths (1, 2 and 4 buckets) and of the range
+# that takes them, columns that give one slice per thread, two, and too many,
+# few buckets (long runs in every block, some over the counting sort's limit),
+# every row in one bucket, and columns that are not 16-byte aligned.  Bit-exact.
+@pytest.mark.parametrize("d,n,k,dt,hmap", [
+    (4095, 3, 40, np.float64, "uniform"), (4096, 3, 40, np.float64, "uniform"),
+    (4097, 5, 4096, np.float64, "uniform"), (8191, 2, 4097, np.float32, "uniform"),
+    (8192, 2, 8192, np.float64, "uniform"), (20483, 9, 8193, np.float64, "uniform"),
+    (12289, 66, 16384, np.float64, "uniform"), (9001, 130, 2048, np.float32, "uniform"),
+    (9001, 130, 8192, np.float64, "uniform"), (9001, 3, 16385, np.float64, "uniform"),
+    (50001, 4, 31, np.float64, "uniform"), (50001, 4, 32, np.float32, "uniform"),
+    (30001, 2, 512, np.float64, "one"), (30001, 2, 5000, np.float32, "last"),
+    (40003, 70, 3001, np.float64, "blocks")])
+def test_sorted_slices_bit_exact(ms, orc, d, n, k, dt, hmap):
+    print("sorted slices d=%d n=%d k=%d %s %s" % (d, n, k, dt.__name__, hmap), flush=True)
+    A = synth.normal_matrix(d, n, seed=d + k, dtype=dt)
+    h = {"uniform": lambda: synth.bucket_map(d, k, seed=d),
+         "one": lambda: np.full(d, k // 2, dtype=np.int32),
+         "last": lambda: np.full(d, k - 1, dtype=np.int32),
+         "blocks": lambda: (np.arange(d) // 700 % k).astype(np.int32)}[hmap]()
+    s = synth.signs(d, seed=d + 1)
+    Y, ws = ms.countsketch_apply(to_dev(A), to_dev(h), to_dev(s), k, mode="sorted")
+    ms.check_status(ws)
+    assert bits_equal(to_host(Y), np.asfortranarray(orc.countsketch(A, h, s, k)))
+
+
+def test_sorted_slices_special_values(ms, orc):
+    # infinities, NaN, signed zeros and the smallest subnormal keep their bits
+    # (a thread adds +0.0 to the sums of its other buckets)
+    d, n, k = 9000, 3, 6000
+    A = synth.normal_matrix(d, n, seed=2)
+    A[::7] = -0.0
+    A[5::97, 0] = np.inf
+    A[11::501, 1] = -np.inf
+    A[3::1009, 2] = 5e-324
+    h, s = synth.bucket_map(d, k, seed=3), synth.signs(d, seed=4)
+    Y, ws = ms.countsketch_apply(to_dev(A), to_dev(h), to_dev(s), k, mode="sorted")
+    ms.check_status(ws)
+    Yg, Yr = to_host(Y), np.asfortranarray(orc.countsketch(A, h, s, k))
+    assert np.array_equal(np.isnan(Yg), np.isnan(Yr))
+    ok = ~np.isnan(Yr)
+    assert bits_equal(Yg[ok], Yr[ok])
