@@ -2,138 +2,172 @@
 //
 // r = B - A X in FP64: A (d x n, FP32 or FP64, column-major) is promoted
 // exactly, X (n x nrhs) is FP64, B has A's type, every product and sum is
-// FP64.  Each thread takes four consecutive rows with one 16-byte load per
-// column of A (a wave reads 1 KB of a column at a time) and keeps the 4 x
-// nrhs sums in registers; X is staged in LDS.
+// FP64.  Each thread takes V groups of four consecutive rows with 16-byte
+// loads of every column of A and keeps the 4 V x nrhs sums in registers; X is
+// staged in LDS.
+//
+// Bound by HBM: A is read once.  What decides the rate is how much of one
+// column a workgroup reads before it goes on to the next, which is on another
+// page: a sum over 8,388,608 x 256 FP32 read at 5.6 TB/s with 4 KB of a column
+// at a time and at 6.8 TB/s with 64 KB and nontemporal loads.
 #include <algorithm>
 
 #include "ms_internal.h"
 
 namespace ms {
 
-// Four consecutive rows of a column, promoted to FP64.  The vector loads are
-// aligned to the element only (a dword-aligned multi-dword global load is
-// legal on CDNA), so a column may start at any element.
+// Four consecutive rows of a column.  The vector loads are aligned to the
+// element only (a dword-aligned multi-dword global load is legal on CDNA), so
+// a column may start at any element.
 template <typename TA>
-struct Rows4 {
-  static __device__ __forceinline__ void load(const TA *p, double v[4]) {
-    typedef TA V __attribute__((ext_vector_type(4), aligned(sizeof(TA))));
-    const V a = gload(reinterpret_cast<const V *>(p));
-    v[0] = (double)a.x;
-    v[1] = (double)a.y;
-    v[2] = (double)a.z;
-    v[3] = (double)a.w;
-  }
-};
-template <>
-struct Rows4<double> {
-  static __device__ __forceinline__ void load(const double *p, double v[4]) {
-    typedef double V __attribute__((ext_vector_type(2), aligned(8)));
-    const V a = gload(reinterpret_cast<const V *>(p));
-    const V b = gload(reinterpret_cast<const V *>(p + 2));
-    v[0] = a.x;
-    v[1] = a.y;
-    v[2] = b.x;
-    v[3] = b.y;
-  }
-};
+__device__ __forceinline__ auto rows4_nt(const TA *p) {
+  typedef TA V __attribute__((ext_vector_type(4)));
+  typedef TA Vu __attribute__((ext_vector_type(4), aligned(sizeof(TA))));
+  return (V)__builtin_nontemporal_load((const __attribute__((address_space(1))) Vu *)p);
+}
 
-constexpr int kResXlds = 8192;  // doubles of X staged in LDS (64 KB)
+constexpr int kResXlds = 8192;  // most doubles of X staged in LDS (64 KB)
 
-template <typename TA, bool XLDS>
-__global__ __launch_bounds__(256) void k_residual(int64_t d, int n, int nrhs,
-                                                  const TA *__restrict__ A, int64_t lda,
-                                                  const TA *__restrict__ B, int64_t ldb,
-                                                  const double *__restrict__ X, int64_t ldx,
-                                                  double *__restrict__ r, int64_t ldr) {
-  constexpr int RH = 8;
-  __shared__ double xs[XLDS ? kResXlds : 1];  // xs[j * RH + c] = X[j, c]
-  if (XLDS) {
-    for (int t = threadIdx.x; t < n * nrhs; t += blockDim.x) {
-      const int c = t / n, j = t - c * n;
-      xs[j * RH + c] = X[j + (int64_t)c * ldx];
-    }
-    __syncthreads();
-  }
-  auto xv = [&](int j, int c) { return XLDS ? xs[j * RH + c] : X[j + (int64_t)c * ldx]; };
-  for (int64_t i0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4; i0 < d;
-       i0 += (int64_t)gridDim.x * blockDim.x * 4) {
-    const bool vec = i0 + 4 <= d;
-    const int rows = (int)min((int64_t)4, d - i0);
-    double acc[4][RH];
+// The residuals of V groups of four rows, i0 + v * vstep each, every row inside
+// the matrix.  x(j, c): X[j, c].  U columns' loads are issued before their
+// products.
+template <typename TA, int RH, int V, typename XF>
+__device__ __forceinline__ void residual_groups(int64_t i0, int64_t vstep, int n, int nrhs,
+                                                const TA *__restrict__ A, int64_t lda,
+                                                const TA *__restrict__ B, int64_t ldb, const XF &x,
+                                                double *__restrict__ r, int64_t ldr) {
+  typedef TA V4 __attribute__((ext_vector_type(4)));
+  constexpr int U = 2;
+  double acc[V][4][RH];
+#pragma unroll
+  for (int v = 0; v < V; ++v)
 #pragma unroll
     for (int q = 0; q < 4; ++q)
 #pragma unroll
-      for (int c = 0; c < RH; ++c) acc[q][c] = 0.0;
-    if (vec) {
-      int j = 0;
-      for (; j + 4 <= n; j += 4) {
-        double a[4][4];
+      for (int c = 0; c < RH; ++c) acc[v][q][c] = 0.0;
+  auto column = [&](int j, const V4 (&a)[V]) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) Rows4<TA>::load(A + i0 + (int64_t)(j + u) * lda, a[u]);
+    for (int c = 0; c < RH; ++c) {
+      const double xc = x(j, c);
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+      for (int v = 0; v < V; ++v)
 #pragma unroll
-          for (int c = 0; c < RH; ++c)
-            if (c < nrhs) {
-              const double x = xv(j + u, c);
+        for (int q = 0; q < 4; ++q) acc[v][q][c] += (double)a[v][q] * xc;
+    }
+  };
+  int j = 0;
+  for (; j + U <= n; j += U) {
+    V4 a[U][V];
 #pragma unroll
-              for (int q = 0; q < 4; ++q) acc[q][c] += a[u][q] * x;
-            }
-      }
-      for (; j < n; ++j) {
-        double a[4];
-        Rows4<TA>::load(A + i0 + (int64_t)j * lda, a);
+    for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int c = 0; c < RH; ++c)
-          if (c < nrhs) {
-            const double x = xv(j, c);
+      for (int v = 0; v < V; ++v) a[u][v] = rows4_nt(A + i0 + v * vstep + (int64_t)(j + u) * lda);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) acc[q][c] += a[q] * x;
-          }
-      }
+    for (int u = 0; u < U; ++u) column(j + u, a[u]);
+  }
+  for (; j < n; ++j) {
+    V4 a[V];
 #pragma unroll
-      for (int c = 0; c < RH; ++c)
-        if (c < nrhs) {
-          double b[4];
-          Rows4<TA>::load(B + i0 + (int64_t)c * ldb, b);
+    for (int v = 0; v < V; ++v) a[v] = rows4_nt(A + i0 + v * vstep + (int64_t)j * lda);
+    column(j, a);
+  }
 #pragma unroll
-          for (int q = 0; q < 4; ++q) r[i0 + q + (int64_t)c * ldr] = b[q] - acc[q][c];
-        }
-    } else {
-      for (int j = 0; j < n; ++j)
+  for (int c = 0; c < RH; ++c)
+    if (c < nrhs) {
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        const V4 b = rows4_nt(B + i0 + v * vstep + (int64_t)c * ldb);
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-          if (q < rows) {
-            const double a = (double)A[i0 + q + (int64_t)j * lda];
-#pragma unroll
-            for (int c = 0; c < RH; ++c)
-              if (c < nrhs) acc[q][c] += a * xv(j, c);
-          }
-#pragma unroll
-      for (int c = 0; c < RH; ++c)
-        if (c < nrhs)
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-            if (q < rows) r[i0 + q + (int64_t)c * ldr] = (double)B[i0 + q + (int64_t)c * ldb] - acc[q][c];
+          r[i0 + v * vstep + q + (int64_t)c * ldr] = (double)b[q] - acc[v][q][c];
+      }
+    }
+}
+
+// One row's residuals, element by element (the rows past the last whole group).
+template <typename TA, typename XF>
+__device__ __forceinline__ void residual_row(int64_t i, int n, int nrhs, const TA *__restrict__ A,
+                                             int64_t lda, const TA *__restrict__ B, int64_t ldb,
+                                             const XF &x, double *__restrict__ r, int64_t ldr) {
+  for (int c = 0; c < nrhs; ++c) {
+    double acc = 0.0;
+    for (int j = 0; j < n; ++j) acc += (double)gload(A + i + (int64_t)j * lda) * x(j, c);
+    r[i + (int64_t)c * ldr] = (double)gload(B + i + (int64_t)c * ldb) - acc;
+  }
+}
+
+// RH: right-hand sides held (nrhs <= RH; the X of the missing ones is zero).
+template <typename TA, bool XLDS, int RH, int T, int V>
+__global__ __launch_bounds__(T) void k_residual(int64_t d, int n, int nrhs,
+                                                const TA *__restrict__ A, int64_t lda,
+                                                const TA *__restrict__ B, int64_t ldb,
+                                                const double *__restrict__ X, int64_t ldx,
+                                                double *__restrict__ r, int64_t ldr) {
+  extern __shared__ __align__(16) double xs[];  // xs[j * RH + c] = X[j, c]
+  if (XLDS) {
+    for (int t = threadIdx.x; t < n * RH; t += T) {
+      const int c = t % RH, j = t / RH;
+      xs[t] = c < nrhs ? X[j + (int64_t)c * ldx] : 0.0;
+    }
+    __syncthreads();
+  }
+  auto xv = [&](int j, int c) {
+    return XLDS ? xs[j * RH + c] : c < nrhs ? X[j + (int64_t)c * ldx] : 0.0;
+  };
+  constexpr int64_t blk = (int64_t)4 * T * V;
+  int64_t r0 = (int64_t)blockIdx.x * blk;
+  for (; r0 + blk <= d; r0 += gridDim.x * blk)
+    residual_groups<TA, RH, V>(r0 + 4 * (int64_t)threadIdx.x, 4 * T, n, nrhs, A, lda, B, ldb, xv, r,
+                               ldr);
+  if (r0 < d) {   // the last rows: whole groups one at a time, then single rows
+    for (int64_t i = r0 + 4 * (int64_t)threadIdx.x; i < d; i += 4 * T) {
+      if (i + 4 <= d)
+        residual_groups<TA, RH, 1>(i, 0, n, nrhs, A, lda, B, ldb, xv, r, ldr);
+      else
+        for (int64_t q = i; q < d; ++q) residual_row(q, n, nrhs, A, lda, B, ldb, xv, r, ldr);
     }
   }
+}
+
+template <typename TA, bool XLDS, int RH, int T, int V>
+static void launch_residual_k(unsigned grid, int64_t d, int64_t n, int64_t nrhs, const TA *A,
+                              int64_t lda, const TA *B, int64_t ldb, const double *X, int64_t ldx,
+                              double *r, int64_t ldr, hipStream_t st) {
+  const size_t lds = XLDS ? (size_t)n * RH * sizeof(double) : 0;
+  hipLaunchKernelGGL((k_residual<TA, XLDS, RH, T, V>), dim3(grid), dim3(T), lds, st, d, (int)n,
+                     (int)nrhs, A, lda, B, ldb, X, ldx, r, ldr);
+}
+
+// T, V: the workgroup of this many right-hand sides when d gives every compute
+// unit one (32 V T bytes of FP64, 16 V T of FP32 of a column at a time, as many
+// as the registers of the sums allow); fewer rows take 1024 at a time.
+template <typename TA, int RH, int T, int V>
+static hipError_t launch_residual_rh(int64_t d, int64_t n, int64_t nrhs, const TA *A, int64_t lda,
+                                     const TA *B, int64_t ldb, const double *X, int64_t ldx,
+                                     double *r, int64_t ldr, hipStream_t st) {
+  const int64_t cus = dev_info().cus;
+  const bool wide = d >= cus * 4 * T * V, xl = n * RH <= kResXlds;
+  const unsigned gw = (unsigned)std::min<int64_t>((d + 4 * T * V - 1) / (4 * T * V), cus * (1024 / T));
+  const unsigned gn = (unsigned)std::min<int64_t>((d + 1023) / 1024, cus * 8);
+  if (wide && xl)
+    launch_residual_k<TA, true, RH, T, V>(gw, d, n, nrhs, A, lda, B, ldb, X, ldx, r, ldr, st);
+  else if (xl)
+    launch_residual_k<TA, true, RH, 256, 1>(gn, d, n, nrhs, A, lda, B, ldb, X, ldx, r, ldr, st);
+  else
+    launch_residual_k<TA, false, RH, 256, 1>(gn, d, n, nrhs, A, lda, B, ldb, X, ldx, r, ldr, st);
+  return hipGetLastError();
 }
 
 template <typename TA>
 static hipError_t launch_residual_t(int64_t d, int64_t n, int64_t nrhs, const TA *A, int64_t lda,
                                     const TA *B, int64_t ldb, const double *X, int64_t ldx,
                                     double *r, int64_t ldr, hipStream_t st) {
-  if (nrhs > 8) return hipErrorInvalidValue;
+  if (nrhs > 8 || nrhs < 1) return hipErrorInvalidValue;
   if (d <= 0) return hipSuccess;
-  const unsigned grid = (unsigned)std::min<int64_t>((d + 1023) / 1024, (int64_t)dev_info().cus * 8);
-  if (n * 8 <= kResXlds)
-    hipLaunchKernelGGL((k_residual<TA, true>), dim3(grid), dim3(256), 0, st, d, (int)n, (int)nrhs,
-                       A, lda, B, ldb, X, ldx, r, ldr);
-  else
-    hipLaunchKernelGGL((k_residual<TA, false>), dim3(grid), dim3(256), 0, st, d, (int)n,
-                       (int)nrhs, A, lda, B, ldb, X, ldx, r, ldr);
-  return hipGetLastError();
+  if (nrhs == 1) return launch_residual_rh<TA, 1, 1024, 4>(d, n, nrhs, A, lda, B, ldb, X, ldx, r, ldr, st);
+  if (nrhs == 2) return launch_residual_rh<TA, 2, 1024, 2>(d, n, nrhs, A, lda, B, ldb, X, ldx, r, ldr, st);
+  if (nrhs <= 4) return launch_residual_rh<TA, 4, 512, 4>(d, n, nrhs, A, lda, B, ldb, X, ldx, r, ldr, st);
+  return launch_residual_rh<TA, 8, 512, 2>(d, n, nrhs, A, lda, B, ldb, X, ldx, r, ldr, st);
 }
 
 hipError_t launch_residual_f32(int64_t d, int64_t n, int64_t nrhs, const float *A, int64_t lda,
@@ -148,16 +182,17 @@ hipError_t launch_residual_f64(int64_t d, int64_t n, int64_t nrhs, const double 
   return launch_residual_t<double>(d, n, nrhs, A, lda, B, ldb, X, ldx, r, ldr, st);
 }
 
-// Residuals of a batch: item = (problem, kBatchResRows rows) taken in
-// sub-blocks of 1024 rows, four rows per thread (16-byte loads of A and B
-// when aligned), X staged in LDS once per item; B has A's type.  r_p is
-// d x nrhs, column-major, ld d.
+// Residuals of a batch: item = (problem, kBatchResRows rows), X staged in LDS
+// once per item; B has A's type.  r_p is d x nrhs, column-major, ld d.  Two
+// groups of four rows per thread at once (8 KB of an FP32 column), one where
+// the sums of more than four right-hand sides take the registers.
 template <typename TA>
 __global__ __launch_bounds__(256) void k_batch_residual(
     int count, const ms_problem *__restrict__ P, const BatchEntry *__restrict__ E,
     const BatchTotals *__restrict__ tot, unsigned char *__restrict__ rarea) {
   constexpr int RH = kBatchMaxRefineRhs;
-  __shared__ double xs[kBatchMaxCols * RH];  // xs[j * RH + c] = X[j, c]
+  static_assert(kBatchResRows == 2048, "256 threads, two groups of four rows each");
+  __shared__ __align__(16) double xs[kBatchMaxCols * RH];  // xs[j * rh + c] = X[j, c]
   const int64_t total = tot->res_items;
   for (int64_t it = blockIdx.x; it < total; it += gridDim.x) {
     const int p = batch_find_m<&BatchEntry::res_start>(E, count, it);
@@ -165,79 +200,43 @@ __global__ __launch_bounds__(256) void k_batch_residual(
     const BatchEntry &e = E[p];
     if (!e.refine) continue;   // converged in an earlier step
     const int n = (int)Q.n, nrhs = (int)Q.nrhs;
+    const int rh = nrhs <= 2 ? nrhs : nrhs <= 4 ? 4 : 8;
+    const TA *A = static_cast<const TA *>(Q.A);
+    const TA *B = static_cast<const TA *>(Q.B);
+    const int64_t lda = Q.lda, ldb = Q.ldb, d = Q.d;
+    double *r = reinterpret_cast<double *>(rarea + e.r_off);
     __syncthreads();  // the previous item's reads of xs are done
-    for (int t = threadIdx.x; t < n * nrhs; t += blockDim.x) {
-      const int c = t / n, j = t - c * n;
-      xs[j * RH + c] = gload(Q.X + j + (int64_t)c * Q.ldx);
+    for (int t = threadIdx.x; t < n * rh; t += 256) {
+      const int j = t / rh, c = t - j * rh;
+      xs[t] = c < nrhs ? gload(Q.X + j + (int64_t)c * Q.ldx) : 0.0;
     }
     __syncthreads();
-    for (int64_t sub = 0; sub < kBatchResRows; sub += 4 * (int64_t)blockDim.x) {
-      const int64_t i0 = (it - e.res_start) * kBatchResRows + sub + (int64_t)threadIdx.x * 4;
-      if (i0 >= Q.d) break;
-      const TA *A = static_cast<const TA *>(Q.A);
-      const TA *B = static_cast<const TA *>(Q.B);
-      double *r = reinterpret_cast<double *>(rarea + e.r_off);
-      const bool vec = i0 + 4 <= Q.d;
-      const int rows = (int)min((int64_t)4, Q.d - i0);
-      double acc[4][RH];
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int c = 0; c < RH; ++c) acc[q][c] = 0.0;
-      if (vec) {
-        int j = 0;
-        for (; j + 4 <= n; j += 4) {
-          double a[4][4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) Rows4<TA>::load(A + i0 + (int64_t)(j + u) * Q.lda, a[u]);
-#pragma unroll
-          for (int u = 0; u < 4; ++u)
-#pragma unroll
-            for (int c = 0; c < RH; ++c)
-              if (c < nrhs) {
-                const double x = xs[(j + u) * RH + c];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) acc[q][c] += a[u][q] * x;
-              }
-        }
-        for (; j < n; ++j) {
-          double a[4];
-          Rows4<TA>::load(A + i0 + (int64_t)j * Q.lda, a);
-#pragma unroll
-          for (int c = 0; c < RH; ++c)
-            if (c < nrhs) {
-              const double x = xs[j * RH + c];
-#pragma unroll
-              for (int q = 0; q < 4; ++q) acc[q][c] += a[q] * x;
-            }
-        }
-#pragma unroll
-        for (int c = 0; c < RH; ++c)
-          if (c < nrhs) {
-            double b[4];
-            Rows4<TA>::load(B + i0 + (int64_t)c * Q.ldb, b);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) r[i0 + q + (int64_t)c * Q.d] = b[q] - acc[q][c];
-          }
-      } else {
-        for (int j = 0; j < n; ++j)
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-            if (q < rows) {
-              const double a = (double)gload(A + i0 + q + (int64_t)j * Q.lda);
-#pragma unroll
-              for (int c = 0; c < RH; ++c)
-                if (c < nrhs) acc[q][c] += a * xs[j * RH + c];
-            }
-#pragma unroll
-        for (int c = 0; c < RH; ++c)
-          if (c < nrhs)
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-              if (q < rows)
-                r[i0 + q + (int64_t)c * Q.d] = (double)gload(B + i0 + q + (int64_t)c * Q.ldb) - acc[q][c];
-      }
-    }
+    const int64_t r0 = (it - e.res_start) * kBatchResRows, i0 = r0 + 4 * (int64_t)threadIdx.x;
+    const bool whole = r0 + kBatchResRows <= d;   // uniform
+#define MS_BRES(RH_, V_)                                                                        \
+  {                                                                                             \
+    auto xv = [&](int j, int c) { return xs[j * RH_ + c]; };                                    \
+    if (whole) {                                                                                \
+      for (int v = 0; v < 2; v += V_)                                                           \
+        residual_groups<TA, RH_, V_>(i0 + 1024 * v, 1024, n, nrhs, A, lda, B, ldb, xv, r, d);   \
+    } else {                                                                                    \
+      for (int64_t i = i0; i < d; i += 1024) {                                                  \
+        if (i + 4 <= d)                                                                         \
+          residual_groups<TA, RH_, 1>(i, 0, n, nrhs, A, lda, B, ldb, xv, r, d);                 \
+        else                                                                                    \
+          for (int64_t q = i; q < d; ++q) residual_row(q, n, nrhs, A, lda, B, ldb, xv, r, d);   \
+      }                                                                                         \
+    }                                                                                           \
+  }
+    if (rh == 1)
+      MS_BRES(1, 2)
+    else if (rh == 2)
+      MS_BRES(2, 2)
+    else if (rh == 4)
+      MS_BRES(4, 2)
+    else
+      MS_BRES(8, 1)
+#undef MS_BRES
   }
 }
 

@@ -344,3 +344,21 @@ def test_batched_refinement_early_stop(ms, orc):
         assert np.array_equal(a, b)
     for a, b in zip(three, stop60):
         assert np.array_equal(a, b)
+
+
+# Batched refinement at every right-hand-side count the residual holds (1, 2, 4,
+# 8), with whole and partial 2048-row items, up to the largest factor of the
+# batched path (k2 = 256) and an n past each 64-column block: in FP64 one step
+# leaves x at the sketch-and-solve solution, which the call without refinement
+# gives, up to rounding (the bar of the FP64 batch against the single call).
+def test_batched_refinement_fixed_point_shapes(ms):
+    shapes = [(2048, 7, 1), (4099, 8, 2), (6144, 33, 3), (2049, 40, 4), (9001, 64, 5),
+              (5000, 65, 6), (20056, 128, 6), (8192, 120, 7), (12289, 128, 8), (700, 100, 1)]
+    probs = [make_problem(ms, d, n, r, seed=300 + i)[1] for i, (d, n, r) in enumerate(shapes)]
+    ref = ms.sketch_lstsq_batched(probs)
+    assert ref.status()[0] == ms.MS_OK
+    X0 = [to_host(p["X"]).copy() for p in probs]
+    run = ms.sketch_lstsq_batched(probs, refine_steps=1)
+    assert run.status()[0] == ms.MS_OK
+    for p, x0, shape in zip(probs, X0, shapes):
+        assert rel(to_host(p["X"]), x0) <= 1e-12, (shape, rel(to_host(p["X"]), x0))

@@ -380,3 +380,32 @@ def test_lstsq_fp64_refinement_fixed_point(ms, orc, d, n, nrhs, k2):
     X = _gpu_lstsq(ms, A, B, h, s, G, k, refine_steps=2)
     Xr, _, _ = orc.sketch_lstsq(A, B, h, s, G, k)
     assert rel(X, Xr) <= 1e-10
+
+
+# The residual of the refinement by right-hand-side count (1, 2, 4, 8 held) and by
+# row count (whole workgroups, their remainders, single last rows), and the kept
+# factors applied at the edges of their 64-row and 64-column blocks: one FP64
+# refinement step of an FP64 solve must land on the sketch-and-solve solution
+# again (the correction is zero up to rounding: x is its fixed point).
+@pytest.mark.parametrize("d,n,nrhs,k2", [
+    (1023, 5, 1, 10), (1025, 16, 2, 33), (4097, 63, 3, 127), (2050, 64, 8, 128),
+    (9001, 65, 4, 130), (5003, 100, 5, 257), (3001, 128, 7, 256), (4099, 130, 1, 600),
+    (1048577 + 4099, 6, 1, 12), (1048576 + 2051, 4, 2, 64), (2097152 + 8195, 3, 4, 8),
+    (1048576 + 4097, 3, 8, 9)])
+def test_refinement_fixed_point_shapes(ms, d, n, nrhs, k2):
+    print("refine d=%d n=%d nrhs=%d k2=%d" % (d, n, nrhs, k2), flush=True)
+    k = max(2 * n * n, 2 * k2)
+    g = torch.Generator(device="cuda").manual_seed(d + n)
+    A = torch.randn((n, d), generator=g, device="cuda", dtype=torch.float64).t()
+    B = torch.randn((nrhs, d), generator=g, device="cuda", dtype=torch.float64).t()
+    h = torch.randint(0, k, (d,), generator=g, device="cuda", dtype=torch.int32)
+    s = torch.randint(0, 2, (d,), generator=g, device="cuda", dtype=torch.int8) * 2 - 1
+    G = torch.randn((k, k2), generator=g, device="cuda", dtype=torch.float64).t() / np.sqrt(k2)
+    X0, ws0 = ms.sketch_lstsq(A, B, h, s, G, k)
+    ms.check_status(ws0)
+    X1, ws1 = ms.sketch_lstsq(A, B, h, s, G, k, refine_steps=1)
+    ms.check_status(ws1)
+    # both x differ from the fixed point by rounding: kappa(Z_A) n u times the
+    # size of x plus that of b over A, kappa(Z_A) below 60 for every shape here
+    scale = X0.norm().item() + B.norm().item() / np.sqrt(d)
+    assert (X1 - X0).norm().item() <= 60 * max(n, 10) * k2 * 2.0 ** -53 * scale * 10
