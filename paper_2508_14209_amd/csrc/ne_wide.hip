@@ -363,9 +363,11 @@ __device__ void back_solve(const TriRef &U, int n, int nrhs, double *z, double *
     if (wave < nrhs) {
       double zi = lane < m ? z[wave * 256 + r0 + lane] : 0.0;
       const double dg = ub[lane * kCsL + lane], rc = 1.0 / dg;
+      const bool fine = __all(isfinite(rc));   // (R0's diagonal may be anything)
       for (int t = m - 1; t >= 0; --t) {
         const double q0 = zi * rc;
-        const double q = fma(fma(-q0, dg, zi), rc, q0);   // lane t's unknown
+        double q = fma(fma(-q0, dg, zi), rc, q0);   // lane t's unknown
+        if (!fine) q = zi / dg;
         const double xt = rd_lane(q, t);
         zi = lane == t ? xt : zi - ub[lane * kCsL + t] * xt;   // zero below the diagonal
       }

@@ -872,13 +872,131 @@ hipError_t launch_batch_qr(int count, int max_k2, int max_n, int max_nc, const m
   return hipSuccess;
 }
 
+// One wave, one right-hand side: y (row l + 64 r in lane l's y[r], zero past m)
+// becomes R^{-1} (Q^T y)_{0:n} with the reflectors, tau and R kept in fact (m x
+// n, ld m).  A serial chain of n reflectors and n unknowns, bound by latency:
+// several reflectors (then columns of R) are on their way from L2 while one is
+// applied, every load unconditional; the columns are taken 64 at a time so that
+// only the 64-row block holding the diagonal (and the last block of rows) needs
+// conditions, and the blocks without entries are left out; the division by the
+// diagonal is a product with its reciprocal and one residual correction (a
+// plain division where a reciprocal is not finite).  m = 512, n = 256: 371 us
+// with one column ahead and every block masked, 203 so, 142 with touch_lines.
+template <int RPL>
+__device__ __forceinline__ void wave_apply_solve(int m, int n, const double *__restrict__ fact,
+                                                 const double *__restrict__ tau,
+                                                 double (&y)[RPL]) {
+  constexpr int D = RPL <= 8 ? 4 : 1;   // columns ahead (64 % D == 0), as the registers allow
+  const int lane = threadIdx.x & 63;
+  int row[RPL];
+#pragma unroll
+  for (int r = 0; r < RPL; ++r) row[r] = min(lane + 64 * r, m - 1);
+  double buf[D][RPL], tb[D];
+  // rows of blocks [r0, r1) of column j
+  auto load = [&](int d, int j, int r0, int r1) {
+    const double *col = fact + (int64_t)j * m;
+#pragma unroll
+    for (int r = 0; r < RPL; ++r)
+      if (r >= r0 && r < r1) buf[d][r] = gload(col + row[r]);
+  };
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    load(d, min(d, n - 1), 0, RPL);
+    tb[d] = gload(tau + min(d, n - 1));
+  }
+  // reflector j: v_i = fact[i, j] below the diagonal, 1 on it
+#pragma unroll
+  for (int jb = 0; jb < RPL; ++jb) {
+    const int je = min(n, 64 * (jb + 1));
+    for (int j0 = 64 * jb; j0 < je; j0 += D) {
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        const int j = j0 + d;
+        if (j >= je) break;
+        double v[RPL], dot0 = 0.0, dot1 = 0.0;
+#pragma unroll
+        for (int r = jb; r < RPL; ++r) {
+          const int i = lane + 64 * r;
+          v[r] = buf[d][r];
+          if (64 * (r + 1) > m && i >= m) v[r] = 0.0;   // (first condition uniform)
+          if (r == jb) v[r] = i > j ? v[r] : (i == j ? 1.0 : 0.0);
+          if ((r - jb) & 1)
+            dot1 += v[r] * y[r];
+          else
+            dot0 += v[r] * y[r];
+        }
+        const double w = tb[d] * wave_allsum(dot0 + dot1);
+        load(d, min(j + D, n - 1), jb, RPL);
+        tb[d] = gload(tau + min(j + D, n - 1));
+#pragma unroll
+        for (int r = jb; r < RPL; ++r) y[r] -= w * v[r];
+      }
+    }
+  }
+  // R x = y[0:n)
+  double dg[RPL], rc[RPL];
+  bool fine = true;
+#pragma unroll
+  for (int r = 0; r < RPL; ++r) {
+    const int i = min(lane + 64 * r, n - 1);
+    dg[r] = gload(fact + i + (int64_t)i * m);
+    rc[r] = 1.0 / dg[r];
+    fine &= isfinite(rc[r]);
+  }
+  fine = __all(fine);
+  // column i, i = n - 1 - s: slot s % D
+  int s = 0;
+#pragma unroll
+  for (int d = 0; d < D; ++d) load(d, max(n - 1 - d, 0), 0, RPL);
+#pragma unroll
+  for (int ib = RPL - 1; ib >= 0; --ib) {
+    while (s < n && ((n - 1 - s) >> 6) == ib) {
+      // as many steps as keep the slots' order, then one by one
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        const int i = n - 1 - s;
+        if (i < 64 * ib || (s & (D - 1)) != d) continue;   // uniform
+        const double q0 = y[ib] * rc[ib];
+        double q = fma(fma(-q0, dg[ib], y[ib]), rc[ib], q0);
+        if (!fine) q = y[ib] / dg[ib];
+        const double xi = read_lane(q, i & 63);
+#pragma unroll
+        for (int r = 0; r <= ib; ++r) {
+          const int t = lane + 64 * r;
+          if (r < ib)
+            y[r] -= buf[d][r] * xi;
+          else
+            y[r] = t < i ? y[r] - buf[d][r] * xi : (t == i ? xi : y[r]);
+        }
+        load(d, max(i - D, 0), 0, ib + 1);
+        ++s;
+      }
+    }
+  }
+}
+
+// Reads one word of every 128-byte line of p[0, bytes) with the nt threads t =
+// 0 .. nt - 1: the factors were written through other dies, and a chain that
+// waits for memory at every few columns takes 0.4 us a step; with its lines
+// brought into this die's L2 ahead of it, 0.28.
+__device__ __forceinline__ void touch_lines(const double *p, int64_t count, int t, int nt) {
+  constexpr int kU = 8;
+  const int64_t lines = (count + 15) / 16;
+  for (int64_t l0 = t; l0 < lines; l0 += (int64_t)kU * nt) {
+    double x[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) x[u] = gload(p + 16 * min(l0 + (int64_t)u * nt, lines - 1));
+#pragma unroll
+    for (int u = 0; u < kU; ++u) asm volatile("" ::"v"(x[u]));
+  }
+}
+constexpr int kTouchWaves = 4;   // waves of an apply-solve workgroup that only touch
+
 // Refinement of a batch, one workgroup per problem: zr = the G Yr partials
 // summed in split order; dx = R^{-1} (Q^T zr)_{0:n} with the reflectors, tau
 // and R the first pass kept; X += dx.  One wave per right-hand side, which
-// holds its column in registers (lane l rows l + 64 r); the next reflector
-// (and, in the back substitution, the next column of R) is loaded while the
-// current one is applied.
-__global__ __launch_bounds__(64 * kBatchMaxRefineRhs) void k_batch_apply_solve(
+// holds its column in registers (lane l rows l + 64 r).
+__global__ __launch_bounds__(64 * (kBatchMaxRefineRhs + kTouchWaves)) void k_batch_apply_solve(
     int count, const ms_problem *__restrict__ P, BatchEntry *__restrict__ E,
     const unsigned char *__restrict__ gvarea, const unsigned char *__restrict__ farea,
     int tol_log2) {
@@ -893,14 +1011,19 @@ __global__ __launch_bounds__(64 * kBatchMaxRefineRhs) void k_batch_apply_solve(
   if (m > kBatchMaxK2 || nrhs > kBatchMaxRefineRhs) return;  // excluded by the setup
   const int64_t MN = (int64_t)m * nrhs;
   const double *part = reinterpret_cast<const double *>(gvarea + e.gv_off);
-  for (int t = threadIdx.x; t < MN; t += blockDim.x) {
-    double s = part[t];
-    for (int z = 1; z < e.nsplit; ++z) s = s + part[t + (int64_t)z * MN];
-    zb[t] = s;
-  }
-  __syncthreads();
   const double *fact = reinterpret_cast<const double *>(farea + e.f_off);
   const double *tau = fact + (int64_t)m * n;
+  constexpr int kT = 64 * kBatchMaxRefineRhs;   // threads that solve; the rest touch the factors
+  if ((int)threadIdx.x >= kT) {
+    touch_lines(fact, (int64_t)m * n, threadIdx.x - kT, 64 * kTouchWaves);
+  } else {
+    for (int t = threadIdx.x; t < MN; t += kT) {
+      double s = part[t];
+      for (int z = 1; z < e.nsplit; ++z) s = s + part[t + (int64_t)z * MN];
+      zb[t] = s;
+    }
+  }
+  __syncthreads();
   const int lane = threadIdx.x & 63, c = threadIdx.x >> 6;
   if (c >= nrhs) {
     // waves without a right-hand side only join the convergence check
@@ -913,68 +1036,21 @@ __global__ __launch_bounds__(64 * kBatchMaxRefineRhs) void k_batch_apply_solve(
     const int i = lane + 64 * r;
     y[r] = i < m ? zb[c * m + i] : 0.0;
   }
-  // y <- Q^T y, reflector j: v_i = fact[i, j] below the diagonal, 1 on it
-  auto load_v = [&](int j, double v[RPL]) {
+  wave_apply_solve<RPL>(m, n, fact, tau, y);
+  // X += dx, with both norms
+  double dx2 = 0.0, x2 = 0.0;
 #pragma unroll
-    for (int r = 0; r < RPL; ++r) {
-      const int i = lane + 64 * r;
-      v[r] = (i > j && i < m) ? fact[i + (int64_t)j * m] : (i == j ? 1.0 : 0.0);
-    }
-  };
-  double vn[RPL], tn = n > 0 ? tau[0] : 0.0;
-  if (n > 0) load_v(0, vn);
-  for (int j = 0; j < n; ++j) {
-    double v[RPL];
-#pragma unroll
-    for (int r = 0; r < RPL; ++r) v[r] = vn[r];
-    const double tj = tn;
-    if (j + 1 < n) {
-      load_v(j + 1, vn);
-      tn = tau[j + 1];
-    }
-    double dot = 0.0;
-#pragma unroll
-    for (int r = 0; r < RPL; ++r) dot += v[r] * y[r];
-    const double w = tj * wave_allsum(dot);
-#pragma unroll
-    for (int r = 0; r < RPL; ++r) y[r] -= w * v[r];
-  }
-  // R dx = y[0:n): column i of R is fact[0:i, i] (on and above the diagonal)
-  auto load_r = [&](int i, double col[RPL]) {
-#pragma unroll
-    for (int r = 0; r < RPL; ++r) {
-      const int t = lane + 64 * r;
-      col[r] = t <= i ? fact[t + (int64_t)i * m] : 0.0;
-    }
-  };
-  double rn[RPL];
-  double dx2 = 0.0, x2 = 0.0;   // lane 0: sums over this right-hand side
-  if (n > 0) load_r(n - 1, rn);
-  for (int i = n - 1; i >= 0; --i) {
-    double col[RPL];
-#pragma unroll
-    for (int r = 0; r < RPL; ++r) col[r] = rn[r];
-    if (i > 0) load_r(i - 1, rn);
-    double yl = 0.0, dl = 0.0;
-#pragma unroll
-    for (int r = 0; r < RPL; ++r)
-      if (r == (i >> 6)) {
-        yl = y[r];
-        dl = col[r];
-      }
-    const double xi = read_lane(yl, i & 63) / read_lane(dl, i & 63);
-#pragma unroll
-    for (int r = 0; r < RPL; ++r) {
-      const int t = lane + 64 * r;
-      if (t < i) y[r] -= col[r] * xi;
-    }
-    if (lane == 0) {
-      const double xn = Q.X[i + (int64_t)c * Q.ldx] + xi;
+  for (int r = 0; r < RPL; ++r) {
+    const int i = lane + 64 * r;
+    if (i < n) {
+      const double xn = Q.X[i + (int64_t)c * Q.ldx] + y[r];
       Q.X[i + (int64_t)c * Q.ldx] = xn;
-      dx2 += xi * xi;
+      dx2 += y[r] * y[r];
       x2 += xn * xn;
     }
   }
+  dx2 = wave_allsum(dx2);
+  x2 = wave_allsum(x2);
   if (tol_log2 > 0) {
     // converged when ||dx||_F <= 2^-tol ||X||_F: the later steps skip the
     // problem (its entry's refine flag cleared; the setup of the next
@@ -1000,7 +1076,8 @@ hipError_t launch_batch_apply_solve(int count, const ms_problem *P, BatchEntry *
                                     int *pstatus, int *status, hipStream_t st, int tol_log2) {
   (void)pstatus;
   (void)status;
-  hipLaunchKernelGGL(k_batch_apply_solve, dim3(count), dim3(64 * kBatchMaxRefineRhs), 0, st,
+  hipLaunchKernelGGL(k_batch_apply_solve, dim3(count),
+                     dim3(64 * (kBatchMaxRefineRhs + kTouchWaves)), 0, st,
                      count, P, E, gvarea, farea, tol_log2);
   return hipGetLastError();
 }
@@ -1047,18 +1124,20 @@ __global__ __launch_bounds__(1024) void k_qr_apply_solve(int m, int n, int nrhs,
 }
 
 // The same for m <= 64 * RPL with each right-hand side in one wave's
-// registers (lane l rows l + 64 r); the next reflector, and in the back
-// substitution the next column of R, are loaded while the current one is
-// applied.  Bm is left unchanged.
+// registers (lane l rows l + 64 r), the waves past the right-hand sides
+// touching the factors.  Bm is left unchanged.  Most waves of a workgroup: the
+// registers of more than 256 rows leave room for eight.
+constexpr int as_waves(int rpl) { return rpl <= 4 ? 8 + kTouchWaves : 8; }
 template <int RPL>
-__global__ __launch_bounds__(512) void k_qr_apply_solve_reg(int m, int n, int nrhs,
+__global__ __launch_bounds__(64 * as_waves(RPL)) void k_qr_apply_solve_reg(int m, int n, int nrhs,
                                                              const double *__restrict__ fact,
                                                              const double *__restrict__ tau,
                                                              const double *__restrict__ Bm,
                                                              double *__restrict__ X, int64_t ldx,
                                                              int *status) {
   __shared__ int s_singular;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int nw = min(nrhs, 8), nt = (int)(blockDim.x >> 6) - nw;   // waves that solve, that touch
   if (threadIdx.x == 0) s_singular = 0;
   __syncthreads();
   for (int i = threadIdx.x; i < n; i += blockDim.x) {
@@ -1074,20 +1153,10 @@ __global__ __launch_bounds__(512) void k_qr_apply_solve_reg(int m, int n, int nr
     if (threadIdx.x == 0) record_status(status, MS_ERR_SINGULAR);
     return;
   }
-  auto load_v = [&](int j, double v[RPL]) {
-#pragma unroll
-    for (int r = 0; r < RPL; ++r) {
-      const int i = lane + 64 * r;
-      v[r] = (i > j && i < m) ? fact[i + (int64_t)j * m] : (i == j ? 1.0 : 0.0);
-    }
-  };
-  auto load_r = [&](int i, double col[RPL]) {
-#pragma unroll
-    for (int r = 0; r < RPL; ++r) {
-      const int t = lane + 64 * r;
-      col[r] = t <= i ? fact[t + (int64_t)i * m] : 0.0;
-    }
-  };
+  if (wave >= nw) {
+    touch_lines(fact, (int64_t)m * n, threadIdx.x - 64 * nw, 64 * nt);
+    return;
+  }
   for (int c = wave; c < nrhs; c += nw) {
     double y[RPL];
 #pragma unroll
@@ -1095,46 +1164,11 @@ __global__ __launch_bounds__(512) void k_qr_apply_solve_reg(int m, int n, int nr
       const int i = lane + 64 * r;
       y[r] = i < m ? Bm[i + (int64_t)c * m] : 0.0;
     }
-    double vn[RPL], tn = tau[0];
-    load_v(0, vn);
-    for (int j = 0; j < n; ++j) {
-      double v[RPL];
+    wave_apply_solve<RPL>(m, n, fact, tau, y);
 #pragma unroll
-      for (int r = 0; r < RPL; ++r) v[r] = vn[r];
-      const double tj = tn;
-      if (j + 1 < n) {
-        load_v(j + 1, vn);
-        tn = tau[j + 1];
-      }
-      if (tj == 0.0) continue;
-      double dot = 0.0;
-#pragma unroll
-      for (int r = 0; r < RPL; ++r) dot += v[r] * y[r];
-      const double w = tj * wave_allsum(dot);
-#pragma unroll
-      for (int r = 0; r < RPL; ++r) y[r] -= w * v[r];
-    }
-    double rn[RPL];
-    load_r(n - 1, rn);
-    for (int i = n - 1; i >= 0; --i) {
-      double col[RPL];
-#pragma unroll
-      for (int r = 0; r < RPL; ++r) col[r] = rn[r];
-      if (i > 0) load_r(i - 1, rn);
-      double yl = 0.0, dl = 0.0;
-#pragma unroll
-      for (int r = 0; r < RPL; ++r)
-        if (r == (i >> 6)) {
-          yl = y[r];
-          dl = col[r];
-        }
-      const double xi = read_lane(yl, i & 63) / read_lane(dl, i & 63);
-#pragma unroll
-      for (int r = 0; r < RPL; ++r) {
-        const int t = lane + 64 * r;
-        if (t < i) y[r] -= col[r] * xi;
-      }
-      if (lane == 0) X[i + (int64_t)c * ldx] = xi;
+    for (int r = 0; r < RPL; ++r) {
+      const int i = lane + 64 * r;
+      if (i < n) X[i + (int64_t)c * ldx] = y[r];
     }
   }
 }
@@ -1143,9 +1177,10 @@ hipError_t launch_qr_apply_solve(int64_t m, int64_t n, int64_t nrhs, const doubl
                                  const double *tau, double *Bm, double *X, int64_t ldx,
                                  int *status, hipStream_t st) {
   if (n < 1 || nrhs < 1) return hipSuccess;
-  const unsigned threads = (unsigned)(64 * std::min<int64_t>(nrhs, 8));
+  const int nw = (int)std::min<int64_t>(nrhs, 8);
 #define MS_AS_CASE(R_)                                                                         \
   if (m <= 64 * R_) {                                                                         \
+    const unsigned threads = 64u * (unsigned)std::min(nw + kTouchWaves, as_waves(R_));         \
     hipLaunchKernelGGL(k_qr_apply_solve_reg<R_>, dim3(1), dim3(threads), 0, st, (int)m, (int)n, \
                        (int)nrhs, fact, tau, (const double *)Bm, X, ldx, status);              \
     return hipGetLastError();                                                                 \
