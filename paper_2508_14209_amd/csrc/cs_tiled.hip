@@ -7,13 +7,27 @@
 // scheme lets every tile's workgroup stream every row and keep the rows of
 // its tile, so each row is decoded and issues a (masked) LDS atomic nbt
 // times.  Here a plan, built once per call from the rows' buckets, groups
-// the rows of every block of 8192 consecutive rows by tile (a stable
+// the rows of every block of 7680 consecutive rows by tile (a stable
 // counting sort inside the block): entry = row offset in the block (13 bits)
 // | bucket within the tile (15 bits) | sign bit.  Tile t's workgroup then
 // visits only its own entries: it reads the entry, gathers that row's value
 // from the column (the rows of an entry list ascend, so a wave's gathers fall
 // in a few cache lines) and adds it to LDS.  Every element is decoded and
 // added once, as in Alg. 2.
+//
+// What bounds it: each tile's workgroup visits nearly every line of A, so a
+// line goes from its die's L2 to nbt compute units, about 18 TB/s over the chip,
+// and the lines must still be in L2 when the last of them comes.  So the waves
+// gather several blocks ahead without conditions (list starts, entries and values each
+// four blocks apart), but a barrier every four blocks keeps them near each
+// other, and few waves take a block (a wave's 64 to 256 consecutive entries share
+// lines).  Before, entries and gathers were waited for in turn.
+//   8,388,608 x 260 FP32, k = 131,072: 5.94 -> 4.25 ms
+//   4,194,304 x 257 FP64, k = 131,072: 3.99 -> 3.59 ms
+//   4,194,304 x 64, k = 65,536, with the plan: FP32 0.69 -> 0.46, FP64 0.85 -> 0.70 ms
+// (Without the barrier, 16 waves to a block: 5.1, 4.1, 0.49 and 0.80 ms; two
+// blocks ahead for four: 4.5, 3.7 ms; whole columns staged through LDS by every
+// tile: 5.1 and 4.5 ms; a line touched ahead by one of the tiles: slower by a quarter.)
 //
 // Schedule: one workgroup per compute unit (the partial sums of a tile take
 // up to 160 KB of LDS), workgroup g on die g % 8.  On each die the
@@ -30,16 +44,18 @@ namespace ms {
 
 namespace {
 
-constexpr int kBlkLog2 = 13;                   // rows per plan block: 8192
-constexpr int64_t kBlk = (int64_t)1 << kBlkLog2;
-constexpr uint32_t kOffMask = (uint32_t)kBlk - 1;
-constexpr int kLbShift = kBlkLog2;             // bucket within the tile: bits 13..27
+constexpr int kWaves = 16;                     // per workgroup
+constexpr int kRowsPerThread = 8;
+constexpr int kPlanThreads = 960;
+constexpr int64_t kBlk = kPlanThreads * kRowsPerThread;   // 7680 rows per plan block
+constexpr int kOffBits = 13;
+constexpr uint32_t kOffMask = (1u << kOffBits) - 1;
+constexpr int kLbShift = kOffBits;             // bucket within the tile: bits 13..27
 constexpr uint32_t kLbMask = 0x7fffu;
 constexpr int64_t kMaxSlots = 20480;           // FP64 partial sums in 160 KB of LDS
 constexpr int kMaxTiles = 32;                  // at least one group per die of 32 CUs
-constexpr int kPlanThreads = 1024;             // 8 rows per thread in a plan block
-constexpr int kUnits = 8;                      // (column, block) units per batch
-constexpr int kPer = 4;                        // gathers in flight per thread
+constexpr int kAhead = 4;                      // of a team's blocks: gathers in flight
+static_assert(kBlk <= kOffMask + 1, "row field");
 
 struct TileShape {
   int nbt = 0;  // 0: not applicable
@@ -53,8 +69,8 @@ TileShape tile_shape(int64_t d, int64_t k) {
   int nbt = 2;
   while (nbt < need) nbt *= 2;
   // two bucket tiles: the untiled kernel, whose two tiles each stream every
-  // row, measured faster (16,777,216 x 129 FP32, k = 32,768: 2.98 vs 3.2 ms);
-  // from four tiles the per-tile entry lists win (k = 131,072: 6.0 vs 7.9 ms)
+  // row, measured faster (16,777,216 x 129 FP32, k = 32,768: 2.67 vs 4.2 ms);
+  // from four tiles the per-tile entry lists win (k = 131,072: 4.3 vs 7.9 ms)
   if (nbt < 4 || nbt > kMaxTiles) return s;
   s.nbt = nbt;
   s.ktile = (k + nbt - 1) / nbt;
@@ -63,81 +79,104 @@ TileShape tile_shape(int64_t d, int64_t k) {
 }
 
 // Per block: the valid rows' entries, tile by tile, each tile's rows
-// ascending (thread i holds rows 8i .. 8i+7 of the block).  boff[b*(nbt+1)+t]
-// = first entry of tile t in the block, boff[b*(nbt+1)+nbt] = valid rows.
+// ascending.  boff[b*(nbt+1)+t] = first entry of tile t in the block,
+// boff[b*(nbt+1)+nbt] = valid rows.  A wave holds 512 rows, 64 at a time; a
+// row's rank among its wave's rows of the tile comes from the ballots of the tile's
+// bits and a running count in LDS, and the waves' counts are summed once per
+// block (a scan over the workgroup per tile, three barriers each, took 74 us for
+// 8,388,608 rows and 8 tiles; this 51 us).
 // SRC as in the LDS CountSketch: stored h and s (checked here), or packed
 // codes from ms_pack_sketch.
 template <bool CODE>
 __global__ __launch_bounds__(kPlanThreads) void k_tile_plan(
     int64_t d, int64_t k, int64_t ktile, int nbt, int64_t nblk, const uint32_t *__restrict__ code,
     const int32_t *__restrict__ h, const int8_t *__restrict__ s, uint32_t *__restrict__ ent,
-    int32_t *__restrict__ boff, int *status) {
-  __shared__ int32_t wave_sum[kPlanThreads / 64];
-  __shared__ int32_t tile_base_s;
+    uint16_t *__restrict__ boff, int *status) {
+  constexpr int kPlanWaves = kPlanThreads / 64;
+  __shared__ uint32_t cnt[kPlanWaves][kMaxTiles];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // a wave's LDS operations are carried out in order; the compiler has to keep them so
+  auto in_order = [] {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
   bool bad = false;
   for (int64_t blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
     const int64_t r0 = blk * kBlk;
-    const int64_t rows = min(kBlk, d - r0);
-    uint32_t w[8];   // entry without the offset field set; 0xffffffff: invalid / absent
-    int tl[8];
+    uint32_t w[kRowsPerThread];   // entry
+    uint32_t tl[kRowsPerThread], pos[kRowsPerThread];
+    bool ok[kRowsPerThread];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int64_t r = (int64_t)tid * 8 + q;
-      tl[q] = -1;
-      w[q] = 0xffffffffu;
-      if (r < rows) {
+    for (int q = 0; q < kRowsPerThread; ++q) {
+      const int rb = (wave * kRowsPerThread + q) * 64 + lane;
+      const int64_t r = r0 + rb;
+      ok[q] = false;
+      w[q] = tl[q] = 0;
+      if (r < d) {
         uint32_t b;
         uint32_t sg;
-        bool ok;
         if (CODE) {
-          const uint32_t e = code[r0 + r];
+          const uint32_t e = code[r];
           b = e & kIdxMask;
           sg = e & kSignBit;
-          ok = (int64_t)b < k;
+          ok[q] = (int64_t)b < k;
         } else {
-          const int32_t hb = h[r0 + r];
-          const int8_t sv = s[r0 + r];
+          const int32_t hb = h[r];
+          const int8_t sv = s[r];
           b = (uint32_t)hb;
           sg = sv < 0 ? kSignBit : 0u;
-          ok = ((uint32_t)hb < (uint32_t)k) & ((sv == 1) | (sv == -1));
+          ok[q] = ((uint32_t)hb < (uint32_t)k) & ((sv == 1) | (sv == -1));
         }
-        bad |= !ok;
-        if (ok) {
-          const uint32_t t = b / (uint32_t)ktile;
-          tl[q] = (int)t;
-          w[q] = (uint32_t)r | ((b - t * (uint32_t)ktile) << kLbShift) | sg;
+        bad |= !ok[q];
+        if (ok[q]) {
+          tl[q] = b / (uint32_t)ktile;
+          w[q] = (uint32_t)rb | ((b - tl[q] * (uint32_t)ktile) << kLbShift) | sg;
         }
       }
     }
-    if (tid == 0) tile_base_s = 0;
-    __syncthreads();
-    for (int t = 0; t < nbt; ++t) {
-      int c = 0;
+    if (lane < kMaxTiles) cnt[wave][lane] = 0;
+    in_order();
 #pragma unroll
-      for (int q = 0; q < 8; ++q) c += tl[q] == t;
-      // exclusive scan of c over the workgroup (thread order = row order)
-      int incl = c;
+    for (int q = 0; q < kRowsPerThread; ++q) {
+      uint64_t same = __ballot(ok[q]);   // the valid rows of this row's tile
+      for (uint32_t bit = 1; bit < (uint32_t)nbt; bit <<= 1) {
+        const uint64_t m = __ballot((tl[q] & bit) != 0);
+        same &= tl[q] & bit ? m : ~m;
+      }
+      pos[q] = cnt[wave][tl[q]] + __popcll(same & ((1ull << lane) - 1));
+      in_order();
+      if (ok[q] && (same >> lane) == 1) cnt[wave][tl[q]] = pos[q] + 1;   // its last row
+      in_order();
+    }
+    __syncthreads();
+    if (wave == 0) {
+      // lane t: the tile's rows before each wave's, then where the tile starts
+      uint32_t sum = 0;
+      if (lane < nbt)
+        for (int v = 0; v < kPlanWaves; ++v) sum += cnt[v][lane];
+      uint32_t incl = sum;
 #pragma unroll
       for (int o = 1; o < 64; o <<= 1) {
-        const int v = __shfl_up(incl, o, 64);
+        const uint32_t v = __shfl_up(incl, o, 64);
         if (lane >= o) incl += v;
       }
-      if (lane == 63) wave_sum[wave] = incl;
-      __syncthreads();
-      int before = tile_base_s;
-      for (int v = 0; v < wave; ++v) before += wave_sum[v];
-      int pos = before + incl - c;
-      if (tid == 0) boff[blk * (nbt + 1) + t] = tile_base_s;
-#pragma unroll
-      for (int q = 0; q < 8; ++q)
-        if (tl[q] == t) ent[r0 + pos++] = w[q];
-      __syncthreads();
-      if (tid == kPlanThreads - 1) tile_base_s = pos;
-      __syncthreads();
+      if (lane < nbt) {
+        uint32_t at = incl - sum;
+        boff[blk * (nbt + 1) + lane] = (uint16_t)at;
+        if (lane == nbt - 1) boff[blk * (nbt + 1) + nbt] = (uint16_t)incl;
+        for (int v = 0; v < kPlanWaves; ++v) {
+          const uint32_t c = cnt[v][lane];
+          cnt[v][lane] = at;
+          at += c;
+        }
+      }
     }
-    if (tid == 0) boff[blk * (nbt + 1) + nbt] = tile_base_s;
     __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kRowsPerThread; ++q)
+      if (ok[q]) ent[r0 + cnt[wave][tl[q]] + pos[q]] = w[q];
+    in_order();
   }
   if (bad) record_status(status, MS_ERR_RANGE);
 }
@@ -161,14 +200,20 @@ __device__ __forceinline__ void tiled_flush(double *acc, uint32_t kt, int64_t bb
   __syncthreads();
 }
 
-template <typename T>
-__global__ __launch_bounds__(1024) void k_cs_tiled(int64_t d, Cols<T> cols, int64_t k,
-                                                   int64_t ktile, int nbt, int64_t nblk,
-                                                   const uint32_t *__restrict__ ent,
-                                                   const int32_t *__restrict__ boff, int xcds,
-                                                   int subs, T *__restrict__ Y, int64_t ldy) {
+// W waves, a team, take a block's list, 64 E consecutive entries each, and the 16 / W
+// teams take turns at the blocks; what is left of a longer list goes by itself.
+template <typename T, int W, int E>
+__global__ __launch_bounds__(64 * kWaves) void k_cs_tiled(
+    int64_t d, Cols<T> cols, int64_t k, int64_t ktile, int nbt, int64_t nblk,
+    const uint32_t *__restrict__ ent, const uint16_t *__restrict__ boff, int xcds, int subs,
+    T *__restrict__ Y, int64_t ldy) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   double *acc = reinterpret_cast<double *>(smem_raw);
+  constexpr int kTeams = kWaves / W;
+  typedef uint64_t U8 __attribute__((aligned(4)));
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int team = wave / W, first = (wave % W) * 64 * E + lane;   // position of the first entry
   const int g = blockIdx.x;
   const int x = g % xcds, slot = g / xcds;
   if (slot >= subs * nbt) return;
@@ -183,77 +228,107 @@ __global__ __launch_bounds__(1024) void k_cs_tiled(int64_t d, Cols<T> cols, int6
   const int64_t total = (int64_t)cols.ncols * nblk;
   int64_t u = total * grp / ngroups;
   const int64_t u1 = total * (grp + 1) / ngroups;
-  int cur = -1;
+  auto add = [&](T a, uint32_t e) {
+    atomicAdd(&acc[(e >> kLbShift) & kLbMask], (double)apply_sign(a, e));
+  };
   while (u < u1) {
     const int c = (int)(u / nblk);
-    const int64_t b0 = u - (int64_t)c * nblk;
-    const int64_t nb = min<int64_t>(kUnits, min(u1 - u, nblk - b0));
-    if (c != cur) {
-      if (cur >= 0) tiled_flush<T>(acc, kt, bbase, cur, Y, ldy);
-      cur = c;
-    }
+    const int64_t b0 = u - (int64_t)c * nblk, b1 = min(nblk, b0 + (u1 - u));
     const T *col = tcol(cols, c);
-    // the batch's entry lists, concatenated: unit j holds virtual positions
-    // [pre[j], pre[j+1])
-    int32_t e0[kUnits], pre[kUnits + 1];
-    pre[0] = 0;
+    // this team's blocks: b0 + team + kTeams i, i < nb
+    const int nb = (int)((b1 - b0 - team + kTeams - 1) / kTeams);
+    const int steps = (int)((b1 - b0 + kTeams - 1) / kTeams);   // the same for all teams
+    const int64_t bb = min(b0 + team, b1 - 1);
+    // In flight: block i + j: values and their entries; block i + j + kAhead:
+    // entries; block i + j + 2 kAhead: where its list starts and ends.  Past the
+    // last block the last one again, its entries not used: without conditions
+    // the loads stay in flight.
+    const T *pv = col + bb * kBlk;
+    const uint32_t *pe = ent + bb * kBlk;
+    uint32_t pr = (uint32_t)(bb * (nbt + 1)) + t;   // of boff, in elements
+    T v[kAhead][E];
+    uint32_t e[kAhead][E], en[kAhead][E];
+    uint64_t rw[kAhead];
+    int len[kAhead], lenn[kAhead], an[kAhead], as[kAhead];
+    auto ranges = [&](int j, int i) {
+      // the two u16 are in the eight bytes from the word that holds the first
+      rw[j] = *(const __attribute__((address_space(4))) U8 *)(uintptr_t)(boff + (pr & ~1u)) >>
+              (16 * (pr & 1));
+      pr += i < nb - 1 ? kTeams * (nbt + 1) : 0;
+    };
+    auto entries = [&](int j, int i) {
+      const int a = (int)(rw[j] & 0xffff), z = (int)(rw[j] >> 16 & 0xffff);
+      an[j] = a;
+      lenn[j] = i < nb ? z - a : 0;
 #pragma unroll
-    for (int j = 0; j < kUnits; ++j) {
-      int32_t a = 0, z = 0;
-      if (j < nb) {
-        const int32_t *bo = boff + (b0 + j) * (nbt + 1) + t;
-        a = bo[0];
-        z = bo[1];
+      for (int q = 0; q < E; ++q)
+        en[j][q] = gload(pe + (uint32_t)min(a + first + 64 * q, max(z - 1, 0)));
+      pe += i < nb - 1 ? kTeams * kBlk : 0;
+    };
+    auto values = [&](int j, int i) {
+      as[j] = an[j];
+      len[j] = lenn[j];
+#pragma unroll
+      for (int q = 0; q < E; ++q) {
+        // a copy that the compiler can't put off to the loop's end, where it
+        // would wait for the load that follows into en
+        asm volatile("v_mov_b32 %0, %1" : "=v"(e[j][q]) : "v"(en[j][q]));
+        v[j][q] = gload(pv + (first + 64 * q < len[j] ? e[j][q] & kOffMask : 0u));
       }
-      e0[j] = a;
-      pre[j + 1] = pre[j] + (z - a);
+      pv += i < nb - 1 ? kTeams * kBlk : 0;
+    };
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) ranges(j, j);
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) {
+      entries(j, j);
+      ranges(j, j + kAhead);
+      __builtin_amdgcn_sched_barrier(0);   // in this order: the next wait is for the oldest
     }
-    const int32_t L = pre[kUnits];
-    for (int32_t base = 0; base < L; base += kPer * (int32_t)blockDim.x) {
-      uint32_t e[kPer];
-      int64_t rb[kPer];
 #pragma unroll
-      for (int p = 0; p < kPer; ++p) {
-        const int32_t v = base + p * (int32_t)blockDim.x + (int32_t)threadIdx.x;
-        e[p] = 0xffffffffu;
-        rb[p] = 0;
-        if (v < L) {
-          // the unit holding v: the last j with pre[j] <= v (static indices
-          // only, so the small arrays stay in registers)
-          int j = 0;
-          int32_t ej = e0[0], pj = 0;
+    for (int j = 0; j < kAhead; ++j) {
+      values(j, j);
+      entries(j, j + kAhead);
+      ranges(j, j + 2 * kAhead);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    for (int i = 0; i < steps; i += kAhead) {
+      // the teams stay near each other: the lines that a die's groups read at a
+      // time fit its L2
+      __builtin_amdgcn_s_barrier();
 #pragma unroll
-          for (int q = 1; q < kUnits; ++q)
-            if (v >= pre[q]) {
-              j = q;
-              ej = e0[q];
-              pj = pre[q];
-            }
-          const int64_t blk = b0 + j;
-          e[p] = gload(ent + blk * kBlk + ej + (v - pj));
-          rb[p] = blk * kBlk;
+      for (int j = 0; j < kAhead; ++j) {
+#pragma unroll
+        for (int q = 0; q < E; ++q)
+          if (first + 64 * q < len[j]) add(v[j][q], e[j][q]);
+        if (len[j] > 64 * W * E) {   // uniform: the rest of a long list
+          const int64_t r = (bb + (int64_t)kTeams * (i + j)) * kBlk;
+          for (int p = 64 * (W * E + wave % W) + lane; p < len[j]; p += 64 * W) {
+            const uint32_t ep = gload(ent + r + as[j] + p);
+            add(gload(col + r + (ep & kOffMask)), ep);
+          }
         }
+        values(j, i + j + kAhead);
+        entries(j, i + j + 2 * kAhead);
+        ranges(j, i + j + 3 * kAhead);
+        __builtin_amdgcn_sched_barrier(0);
       }
-      T a[kPer];
-#pragma unroll
-      for (int p = 0; p < kPer; ++p)
-        a[p] = e[p] != 0xffffffffu ? gload(col + rb[p] + (e[p] & kOffMask)) : T(0);
-#pragma unroll
-      for (int p = 0; p < kPer; ++p)
-        if (e[p] != 0xffffffffu)
-          atomicAdd(&acc[(e[p] >> kLbShift) & kLbMask], (double)apply_sign(a[p], e[p]));
     }
-    u += nb;
+    u += b1 - b0;
+    tiled_flush<T>(acc, kt, bbase, c, Y, ldy);
   }
-  if (cur >= 0) tiled_flush<T>(acc, kt, bbase, cur, Y, ldy);
 }
+
+// Bytes of the entries (a multiple of 8192 rows), which the u16 list starts follow;
+// the kernel reads a start in eight bytes, up to four past the last one.
+size_t entry_bytes(int64_t d) { return align_up((size_t)((d + 8191) / 8192) * 8192 * 4); }
 
 }  // namespace
 
 size_t cs_tile_plan_bytes(int64_t d, int64_t k) {
   const TileShape s = tile_shape(d, k);
   if (!s.nbt) return 0;
-  return align_up((size_t)s.nblk * kBlk * 4) + align_up((size_t)s.nblk * (s.nbt + 1) * 4);
+  return entry_bytes(d) + align_up((size_t)s.nblk * (s.nbt + 1) * 2 + 4);
 }
 
 bool cs_tiled_supported(int64_t d, int64_t k) {
@@ -268,8 +343,8 @@ hipError_t launch_tile_plan(int64_t d, int64_t k, const uint32_t *code, const in
   const TileShape sh = tile_shape(d, k);
   if (!sh.nbt) return hipErrorInvalidValue;
   uint32_t *ent = static_cast<uint32_t *>(plan);
-  int32_t *boff = reinterpret_cast<int32_t *>(static_cast<unsigned char *>(plan) +
-                                              align_up((size_t)sh.nblk * kBlk * 4));
+  uint16_t *boff =
+      reinterpret_cast<uint16_t *>(static_cast<unsigned char *>(plan) + entry_bytes(d));
   const unsigned grid = (unsigned)std::min<int64_t>(sh.nblk, 4096);
   if (code)
     hipLaunchKernelGGL(k_tile_plan<true>, dim3(grid), dim3(kPlanThreads), 0, st, d, k, sh.ktile,
@@ -290,15 +365,26 @@ hipError_t launch_cs_tiled(int64_t d, int64_t k, const Cols<T> &c, const void *p
   const int xcds = di.xcds;
   const int subs = di.cus / xcds / sh.nbt;
   const size_t lds = (size_t)sh.ktile * 8;
-  const void *fn = (const void *)k_cs_tiled<T>;
-  hipError_t e = allow_dynamic_lds(fn, (int)lds);
-  if (e != hipSuccess) return e;
   const uint32_t *ent = static_cast<const uint32_t *>(plan);
-  const int32_t *boff = reinterpret_cast<const int32_t *>(
-      static_cast<const unsigned char *>(plan) + align_up((size_t)sh.nblk * kBlk * 4));
-  hipLaunchKernelGGL(k_cs_tiled<T>, dim3((unsigned)(xcds * subs * sh.nbt)), dim3(1024), lds, st,
-                     d, c, k, sh.ktile, sh.nbt, sh.nblk, ent, boff, xcds, subs, Y, ldy);
-  return hipGetLastError();
+  const uint16_t *boff = reinterpret_cast<const uint16_t *>(
+      static_cast<const unsigned char *>(plan) + entry_bytes(d));
+  auto go = [&](auto kern) -> hipError_t {
+    const hipError_t e = allow_dynamic_lds((const void *)kern, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(xcds * subs * sh.nbt)), dim3(64 * kWaves), lds, st, d,
+                       c, k, sh.ktile, sh.nbt, sh.nblk, ent, boff, xcds, subs, Y, ldy);
+    return hipGetLastError();
+  };
+  // 64 W E entries hold a list of 7680 / nbt on average and two deviations; the
+  // fewer waves to a block the better (8 tiles, FP32 as above: 16 waves 4.7, 8 waves
+  // 4.5, 4 waves 4.3 ms), up to four entries a lane (2 waves, 8 entries: 4.5 ms;
+  // with 4 tiles all measured alike)
+  switch (sh.nbt) {
+    case 4: return go(k_cs_tiled<T, 16, 2>);
+    case 8: return go(k_cs_tiled<T, 4, 4>);
+    case 16: return go(k_cs_tiled<T, 4, 2>);
+    default: return go(k_cs_tiled<T, 2, 2>);
+  }
 }
 template hipError_t launch_cs_tiled<double>(int64_t, int64_t, const Cols<double> &, const void *,
                                             double *, int64_t, hipStream_t);

@@ -584,7 +584,7 @@ __device__ __forceinline__ void sort4096_lds(uint32_t *key) {
 }
 
 // cs_tiled.hip -- the CountSketch for bucket counts beyond one workgroup's
-// LDS (k > 16384): a per-call plan grouping each 8192-row block's rows by
+// LDS (k > 16384): a per-call plan grouping each 7680-row block's rows by
 // bucket tile, then one pass in which each tile's workgroups visit only
 // their own rows.
 // Bytes of the plan (0 when the tiled CountSketch does not apply to d, k).

@@ -154,6 +154,30 @@ def test_countsketch_tiled_plan(ms, orc, d, n, k, dtype, tiled):
     assert rel(to_host(Y), orc.countsketch(A, h, s, k)) <= (1e-12 if dtype == np.float64 else 1e-5)
 
 
+@pytest.mark.parametrize("d,n,k,dtype,one", [
+    (7679, 3, 65536, np.float32, None), (7680, 2, 131072, np.float64, None),
+    (7681, 5, 131072, np.float32, None), (7680 * 21 + 1, 37, 163841, np.float32, None),
+    (7680 * 40, 3, 327681, np.float64, None), (100003, 9, 655360, np.float32, None),
+    (61441, 3, 65536, np.float64, 1), (61441, 3, 131072, np.float32, 7),
+    (30011, 2, 262144, np.float64, 15), (30011, 2, 600000, np.float32, 31)])
+def test_countsketch_tile_lists(ms, orc, d, n, k, dtype, one):
+    # The lists of 4, 8, 16 and 32 bucket tiles: row blocks that end just before, at
+    # and after a plan block's 7680 rows, fewer blocks than teams of waves, shares
+    # that leave a column midway, and (one) all rows in one tile, whose lists are
+    # longer than what a team takes at a time.
+    print("tile lists d=%d n=%d k=%d %s %s" % (d, n, k, np.dtype(dtype), one), flush=True)
+    A, h, s = _inputs(d, n, k, seed=d % 97, dtype=dtype)
+    if one is not None:
+        nbt = 4
+        while nbt * 20480 < k:
+            nbt *= 2
+        kt = -(-k // nbt)
+        h = (one * kt + h % (min(kt, k - one * kt))).astype(h.dtype)
+    Y, ws = ms.countsketch_apply(to_dev(A), to_dev(h), to_dev(s), k, mode="lds")
+    ms.check_status(ws)
+    assert rel(to_host(Y), orc.countsketch(A, h, s, k)) <= (1e-12 if dtype == np.float64 else 1e-5)
+
+
 @pytest.mark.parametrize("dtype", [np.float64, np.float32])
 def test_countsketch_tiled_accumulate_row_blocks(ms, orc, dtype):
     # Y += C A over two row blocks (the streaming form of Sec. 7) through the
