@@ -638,7 +638,16 @@ __device__ __forceinline__ void cs_segment(double *acc, const Cols<T> &cols, int
 // contiguous share of the (column tile, row) space of its rows, so the bucket
 // tiles of a column are streamed by workgroups of the same die at the same
 // time, and each workgroup flushes LDS only when its share crosses a column
-// tile.  PART: the die's groups split its column tiles instead (whole tiles,
+// tile.  With several bucket tiles the groups first take whole column tiles, a
+// set of them at a time, all at the same rows: one group's read of the codes
+// (as many bytes per column as FP32 data, and more than L2 holds) then serves the
+// others, and only the column tiles left over are shared by rows.  Every row
+// is still read once per bucket tile, which bounds it (16,777,216 x 129 FP32, k =
+// 32,768: 2.67 -> 2.53 ms by the sets, 2.46 with six vectors in flight for four, 7.0
+// TB/s of A; 8,388,608 x 65 FP64: 1.17 -> 1.07 ms.  A barrier per step, so that a pair of
+// tiles shares its reads of A: 3.1 ms; with one bucket tile the sets gain nothing and
+// cost 300,000 x 70 FP64, k = 500, 53 -> 57 us).
+// PART: the die's groups split its column tiles instead (whole tiles,
 // all of the die's rows), so each (column, bucket) of a die has one owner,
 // which stores its partial sum into the die's slice of a partial buffer (Y,
 // ld k, slices of k x ncols) with plain stores; k_cs_part_reduce adds the
@@ -678,14 +687,20 @@ __global__ __launch_bounds__(1024) void k_cs_lds_xcd(int64_t d, Cols<T> cols,
     if (bad) record_status(status, MS_ERR_RANGE);
     return;
   }
-  const int64_t total = (int64_t)nct * len;
+  const int sets = nbt > 1 ? nct / subs : 0;
+  for (int q = 0; q < sets; ++q) {
+    const int c0 = (q * subs + sub) * NT;
+    cs_segment<T, NT, VEC, SRC, UNR, NTL>(acc, cols, c0, min(NT, cols.ncols - c0), code, h, s, k,
+                                          b0, kt, R0, R1, Y, ldy, bad);
+  }
+  const int64_t total = (int64_t)(nct - sets * subs) * len;
   int64_t u0 = (total * sub / subs) & ~(int64_t)255;
   const int64_t u1 = sub + 1 == subs ? total : ((total * (sub + 1) / subs) & ~(int64_t)255);
   while (u0 < u1) {
     const int ct = (int)(u0 / len);
     const int64_t rlo = u0 - (int64_t)ct * len;
     const int64_t rhi = min(len, rlo + (u1 - u0));
-    const int c0 = ct * NT;
+    const int c0 = (sets * subs + ct) * NT;
     const int nc = min(NT, cols.ncols - c0);
     cs_segment<T, NT, VEC, SRC, UNR, NTL>(acc, cols, c0, nc, code, h, s, k, b0, kt, R0 + rlo,
                                             R0 + rhi, Y, ldy, bad);
@@ -934,6 +949,7 @@ static hipError_t launch_cs_xcd_v(bool vec, int grid, size_t lds, hipStream_t st
                                   int *status) {
   // vectors in flight per thread: fewer for wider column tiles (registers)
   constexpr int UNR = NT >= 8 ? 1 : NT >= 4 ? 2 : 4;
+  constexpr int UNRT = NT == 1 ? 6 : UNR;   // with several bucket tiles
   if constexpr (NT == 1) {
   if (part && nbt > 1) {
     hipError_t e =
@@ -953,10 +969,10 @@ static hipError_t launch_cs_xcd_v(bool vec, int grid, size_t lds, hipStream_t st
   }
   }
   if (nbt > 1)  // bucket tiles re-read A: ordinary loads, so the die's L2 keeps it
-    return vec ? launch_cs_xcd_k<T, NT, true, SRC, UNR, false, false>(
+    return vec ? launch_cs_xcd_k<T, NT, true, SRC, UNRT, false, false>(
                      grid, lds, st, d, c, code, h, s, k, ktile, nct, nbt, xcds, spx, rpx, Y, ldy,
                      status)
-               : launch_cs_xcd_k<T, NT, false, SRC, UNR, false, false>(
+               : launch_cs_xcd_k<T, NT, false, SRC, UNRT, false, false>(
                      grid, lds, st, d, c, code, h, s, k, ktile, nct, nbt, xcds, spx, rpx, Y, ldy,
                      status);
   return vec ? launch_cs_xcd_k<T, NT, true, SRC, UNR, true, false>(

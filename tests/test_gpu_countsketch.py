@@ -154,6 +154,27 @@ def test_countsketch_tiled_plan(ms, orc, d, n, k, dtype, tiled):
     assert rel(to_host(Y), orc.countsketch(A, h, s, k)) <= (1e-12 if dtype == np.float64 else 1e-5)
 
 
+@pytest.mark.parametrize("d,n,k,dtype", [(100003, 15, 32768, np.float32),
+                                         (100003, 16, 32768, np.float64),
+                                         (60000, 37, 32768, np.float32),
+                                         (2049, 33, 20000, np.float32),
+                                         (260, 49, 40000, np.float64)])
+def test_countsketch_column_sets(ms, orc, d, n, k, dtype):
+    # Several bucket tiles, a workspace of the status block only: no set, whole
+    # sets and left-over columns of the 16 groups (two tiles) or 10 (three), dies
+    # without rows.
+    import torch
+    A, h, s = _inputs(d, n, k, seed=n, dtype=dtype)
+    print("column sets d=%d n=%d k=%d %s" % (d, n, k, np.dtype(dtype)), flush=True)
+    code, _ = ms.pack_sketch(to_dev(h), to_dev(s), k)
+    Y = ms.empty_colmajor(k, n, torch.float64 if dtype == np.float64 else torch.float32, "cuda")
+    Y.zero_()
+    ws = ms.workspace(256, "cuda")
+    ms.countsketch_accumulate(to_dev(A), code, k, Y, mode="lds", ws=ws)
+    ms.check_status(ws)
+    assert rel(to_host(Y), orc.countsketch(A, h, s, k)) <= (1e-12 if dtype == np.float64 else 1e-5)
+
+
 @pytest.mark.parametrize("d,n,k,dtype,one", [
     (7679, 3, 65536, np.float32, None), (7680, 2, 131072, np.float64, None),
     (7681, 5, 131072, np.float32, None), (7680 * 21 + 1, 37, 163841, np.float32, None),
