@@ -641,12 +641,14 @@ __device__ __forceinline__ void cs_segment(double *acc, const Cols<T> &cols, int
 // tile.  With several bucket tiles the groups first take whole column tiles, a
 // set of them at a time, all at the same rows: one group's read of the codes
 // (as many bytes per column as FP32 data, and more than L2 holds) then serves the
-// others, and only the column tiles left over are shared by rows.  Every row
-// is still read once per bucket tile, which bounds it (16,777,216 x 129 FP32, k =
-// 32,768: 2.67 -> 2.53 ms by the sets, 2.46 with six vectors in flight for four, 7.0
-// TB/s of A; 8,388,608 x 65 FP64: 1.17 -> 1.07 ms.  A barrier per step, so that a pair of
-// tiles shares its reads of A: 3.1 ms; with one bucket tile the sets gain nothing and
-// cost 300,000 x 70 FP64, k = 500, 53 -> 57 us).
+// others, and only the column tiles left over are shared by rows.  HBM reads went
+// from 2.3 to 1.23 times the algorithmic bytes; what bounds it now is data and code
+// of every element going from L2 to one compute unit per bucket tile, 14 TB/s in
+// FP32 (16,777,216 x 129 FP32, k = 32,768: 2.67 -> 2.53 ms by the sets, 2.46 with six
+// vectors in flight for four; 8,388,608 x 65 FP64: 1.17 -> 1.07 ms.  A barrier per
+// step: 3.1 ms; values for the next step loaded under this one's adds: 2.54 to 2.72,
+// the more in flight the worse.  With one bucket tile the sets gain nothing and cost
+// 300,000 x 70 FP64, k = 500, 53 -> 57 us).
 // PART: the die's groups split its column tiles instead (whole tiles,
 // all of the die's rows), so each (column, bucket) of a die has one owner,
 // which stores its partial sum into the die's slice of a partial buffer (Y,
