@@ -369,7 +369,8 @@ __device__ void back_solve(const TriRef &U, int n, int nrhs, double *z, double *
         double q = fma(fma(-q0, dg, zi), rc, q0);   // lane t's unknown
         if (!fine) q = zi / dg;
         const double xt = rd_lane(q, t);
-        zi = lane == t ? xt : zi - ub[lane * kCsL + t] * xt;   // zero below the diagonal
+        // (the unknowns below t are solved: zero times an infinite one must not reach them)
+        zi = lane == t ? xt : lane < t ? zi - ub[lane * kCsL + t] * xt : zi;
       }
       if (lane < m) z[wave * 256 + r0 + lane] = zi;
     }

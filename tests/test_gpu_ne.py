@@ -197,3 +197,25 @@ def test_normal_equations_tile_columns(ms, d, n, nrhs, dtype):
     res = A64.T @ B64 - gram @ Xh
     scale = np.linalg.norm(gram) * np.linalg.norm(Xh) + np.linalg.norm(A64.T @ B64)
     assert np.linalg.norm(res) / scale <= 1e-13
+
+
+# One unknown overflows (its column of A is tiny and nothing else is in its rows,
+# so that R is exactly zero beside its diagonal): the others stay what they are.
+# They are the solution of the remaining n - 1 columns, kappa(A) below 2: the
+# Gram matrix's and the solves' rounding, n kappa^2 u (below 5e-14), bar 1e-12.
+@pytest.mark.parametrize("n", [80, 130])
+def test_normal_equations_wide_infinite_unknown(ms, n):
+    d, rows = 4000, 10
+    print("normal_equations infinite unknown n=%d" % n, flush=True)
+    rng = np.random.default_rng(n)
+    A = rng.standard_normal((d, n))
+    A[rows:, 0] = 0.0
+    A[:rows, 1:] = 0.0
+    A[:rows, 0] = 1e-150
+    B = rng.standard_normal((d, 1))
+    B[:rows] = 1e170
+    X, _, ws = ms.normal_equations_lstsq(to_dev(A), to_dev(B))
+    ms.check_status(ws)
+    x = to_host(X)[:, 0]
+    xr = np.linalg.lstsq(A[rows:, 1:], B[rows:, 0], rcond=None)[0]
+    assert rel(x[1:], xr) <= 1e-12
