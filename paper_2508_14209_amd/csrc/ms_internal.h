@@ -487,6 +487,18 @@ __device__ __forceinline__ double read_lane(double v, int lane) {
   const int hi = __builtin_amdgcn_readlane((int)(u >> 32), lane);
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
+// a / b with rc = 1 / b at hand: the product and one residual correction, a shorter
+// chain than a division.  NaN where the quotient or the reciprocal overflows or an
+// operand is infinite: quotient() then divides.
+__device__ __forceinline__ double finite_quotient(double a, double b, double rc) {
+  const double q0 = a * rc;
+  return fma(fma(-q0, b, a), rc, q0);
+}
+__device__ __forceinline__ double quotient(double a, double b, double rc) {
+  double q = finite_quotient(a, b, rc);
+  if (!isfinite(q)) q = a / b;
+  return q;
+}
 // DPP broadcast into the rows selected by ROWMASK; other rows get 0.
 template <int CTRL, int ROWMASK>
 __device__ __forceinline__ double dpp_bcast(double v) {

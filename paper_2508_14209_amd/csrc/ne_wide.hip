@@ -342,9 +342,9 @@ struct TriRef {
 // z (LDS, z[c * 256 + i], nrhs columns) := U^{-1} z for upper-triangular U
 // of order n, by 64 x 64 blocks from the last (all kCbT threads call it; ub:
 // LDS for one block, ps: LDS for kCbT partial sums).  A block's triangle is
-// solved by one wave per right-hand side with an unknown per lane (the
-// division by the diagonal as a product with its reciprocal and one residual
-// correction, so that the chain from one unknown to the next is short); the
+// solved by one wave per right-hand side with an unknown per lane
+// (finite_quotient(), so that the chain from one unknown to the next is short, and
+// once more by divisions if an unknown is not finite); the
 // rows above it are then updated by every thread, a row per thread and a
 // quarter of the block's columns each.
 __device__ void back_solve(const TriRef &U, int n, int nrhs, double *z, double *ub, double *ps) {
@@ -361,17 +361,19 @@ __device__ void back_solve(const TriRef &U, int n, int nrhs, double *z, double *
     }
     __syncthreads();
     if (wave < nrhs) {
-      double zi = lane < m ? z[wave * 256 + r0 + lane] : 0.0;
+      const double z0 = lane < m ? z[wave * 256 + r0 + lane] : 0.0;
       const double dg = ub[lane * kCsL + lane], rc = 1.0 / dg;
-      const bool fine = __all(isfinite(rc));   // (R0's diagonal may be anything)
-      for (int t = m - 1; t >= 0; --t) {
-        const double q0 = zi * rc;
-        double q = fma(fma(-q0, dg, zi), rc, q0);   // lane t's unknown
-        if (!fine) q = zi / dg;
-        const double xt = rd_lane(q, t);
-        // (the unknowns below t are solved: zero times an infinite one must not reach them)
-        zi = lane == t ? xt : lane < t ? zi - ub[lane * kCsL + t] * xt : zi;
-      }
+      auto solve = [&](auto divide) {
+        double zi = z0;
+        for (int t = m - 1; t >= 0; --t) {
+          const double xt = rd_lane(divide(zi), t);   // lane t's unknown
+          // (the unknowns below t are solved: zero times an infinite one must not reach them)
+          zi = lane == t ? xt : lane < t ? zi - ub[lane * kCsL + t] * xt : zi;
+        }
+        return zi;
+      };
+      double zi = solve([&](double a) { return finite_quotient(a, dg, rc); });
+      if (!__all(isfinite(zi))) zi = solve([&](double a) { return a / dg; });
       if (lane < m) z[wave * 256 + r0 + lane] = zi;
     }
     __syncthreads();
@@ -444,8 +446,8 @@ __global__ __launch_bounds__(64) void k_chol_diag(int n, int np, int kb, double 
 // (those of A past the block, then the right-hand sides), one workgroup per 64
 // columns, R_kk and the columns in LDS.  Sixteen rows at a time: the four
 // waves subtract the rows solved before (four rows each, a column per lane),
-// then one wave solves the 16 x 16 triangle (the division by the diagonal as
-// a product with its reciprocal and one residual correction).
+// then one wave solves the 16 x 16 triangle (finite_quotient(); by divisions if
+// something is not finite).
 __global__ __launch_bounds__(kCsT) void k_chol_row(int n, int nc, int np, int kb,
                                                    double *__restrict__ W,
                                                    const int *__restrict__ bad) {
@@ -480,16 +482,21 @@ __global__ __launch_bounds__(kCsT) void k_chol_row(int n, int nc, int np, int kb
     __syncthreads();
     if (wave == 0) {
       double w[16];
+      auto solve = [&](auto divide) {
+        bool finite = true;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) w[r] = xs[(jb + r) * kCsB + lane];
+        for (int r = 0; r < 16; ++r) w[r] = xs[(jb + r) * kCsB + lane];
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const double dg = dk[(jb + i) * kCsB + jb + i], rc = 1.0 / dg;
-        const double q0 = w[i] * rc;
-        w[i] = fma(fma(-q0, dg, w[i]), rc, q0);
+        for (int i = 0; i < 16; ++i) {
+          w[i] = divide(w[i], dk[(jb + i) * kCsB + jb + i]);
+          finite &= isfinite(w[i]);
 #pragma unroll
-        for (int r = i + 1; r < 16; ++r) w[r] -= dk[(jb + i) * kCsB + jb + r] * w[i];
-      }
+          for (int r = i + 1; r < 16; ++r) w[r] -= dk[(jb + i) * kCsB + jb + r] * w[i];
+        }
+        return __all(finite);
+      };
+      if (!solve([](double a, double b) { return finite_quotient(a, b, 1.0 / b); }))
+        solve([](double a, double b) { return a / b; });
 #pragma unroll
       for (int r = 0; r < 16; ++r) xs[(jb + r) * kCsB + lane] = w[r];
     }

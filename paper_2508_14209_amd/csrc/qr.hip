@@ -879,8 +879,7 @@ hipError_t launch_batch_qr(int count, int max_k2, int max_n, int max_nc, const m
 // applied, every load unconditional; the columns are taken 64 at a time so that
 // only the 64-row block holding the diagonal (and the last block of rows) needs
 // conditions, and the blocks without entries are left out; the division by the
-// diagonal is a product with its reciprocal and one residual correction (a
-// plain division where a reciprocal is not finite).  m = 512, n = 256: 371 us
+// diagonal is quotient().  m = 512, n = 256: 371 us
 // with one column ahead and every block masked, 203 so, 142 with touch_lines.
 template <int RPL>
 __device__ __forceinline__ void wave_apply_solve(int m, int n, const double *__restrict__ fact,
@@ -935,15 +934,12 @@ __device__ __forceinline__ void wave_apply_solve(int m, int n, const double *__r
   }
   // R x = y[0:n)
   double dg[RPL], rc[RPL];
-  bool fine = true;
 #pragma unroll
   for (int r = 0; r < RPL; ++r) {
     const int i = min(lane + 64 * r, n - 1);
     dg[r] = gload(fact + i + (int64_t)i * m);
     rc[r] = 1.0 / dg[r];
-    fine &= isfinite(rc[r]);
   }
-  fine = __all(fine);
   // column i, i = n - 1 - s: slot s % D
   int s = 0;
 #pragma unroll
@@ -956,10 +952,7 @@ __device__ __forceinline__ void wave_apply_solve(int m, int n, const double *__r
       for (int d = 0; d < D; ++d) {
         const int i = n - 1 - s;
         if (i < 64 * ib || (s & (D - 1)) != d) continue;   // uniform
-        const double q0 = y[ib] * rc[ib];
-        double q = fma(fma(-q0, dg[ib], y[ib]), rc[ib], q0);
-        if (!fine) q = y[ib] / dg[ib];
-        const double xi = read_lane(q, i & 63);
+        const double xi = read_lane(quotient(y[ib], dg[ib], rc[ib]), i & 63);
 #pragma unroll
         for (int r = 0; r <= ib; ++r) {
           const int t = lane + 64 * r;

@@ -219,3 +219,25 @@ def test_normal_equations_wide_infinite_unknown(ms, n):
     x = to_host(X)[:, 0]
     xr = np.linalg.lstsq(A[rows:, 1:], B[rows:, 0], rcond=None)[0]
     assert rel(x[1:], xr) <= 1e-12
+
+
+# Quotients that overflow are infinite, not NaN: the unknown itself (B = 1e170), and
+# already its component of R^{-T} A^T B (B = 1e300), as the first unknown and as the
+# last.  The tiny column stands alone in its rows, so nothing is subtracted from
+# its own chain.
+@pytest.mark.parametrize("n", [80, 130])
+@pytest.mark.parametrize("col,big", [(0, 1e170), (0, -1e170), (-1, 1e170), (-1, 1e300)])
+def test_normal_equations_wide_overflow_is_infinite(ms, n, col, big):
+    d, rows = 4000, 10
+    print("normal_equations overflow n=%d col=%d big=%g" % (n, col, big), flush=True)
+    A = np.random.default_rng(n).standard_normal((d, n))
+    keep = A[rows:, col].copy()
+    A[:rows] = 0.0
+    A[rows:, col] = 0.0
+    A[:rows, col] = 1e-150
+    B = np.zeros((d, 1))
+    B[rows:, 0] = keep
+    B[:rows] = big
+    X, _, ws = ms.normal_equations_lstsq(to_dev(A), to_dev(B))
+    ms.check_status(ws)
+    assert to_host(X)[col, 0] == np.copysign(np.inf, big)
