@@ -881,7 +881,9 @@ hipError_t launch_batch_qr(int count, int max_k2, int max_n, int max_nc, const m
 // conditions, and the blocks without entries are left out; the division by the
 // diagonal is quotient().  m = 512, n = 256: 371 us
 // with one column ahead and every block masked, 203 so, 142 with touch_lines.
-template <int RPL>
+// SKIP0: a reflector with tau = 0 is left out, whatever y holds (0 times an infinite
+// sum would be NaN).
+template <int RPL, bool SKIP0>
 __device__ __forceinline__ void wave_apply_solve(int m, int n, const double *__restrict__ fact,
                                                  const double *__restrict__ tau,
                                                  double (&y)[RPL]) {
@@ -924,7 +926,8 @@ __device__ __forceinline__ void wave_apply_solve(int m, int n, const double *__r
           else
             dot0 += v[r] * y[r];
         }
-        const double w = tb[d] * wave_allsum(dot0 + dot1);
+        const double sum = wave_allsum(dot0 + dot1);
+        const double w = SKIP0 && tb[d] == 0.0 ? 0.0 : tb[d] * sum;
         load(d, min(j + D, n - 1), jb, RPL);
         tb[d] = gload(tau + min(j + D, n - 1));
 #pragma unroll
@@ -1029,7 +1032,7 @@ __global__ __launch_bounds__(64 * (kBatchMaxRefineRhs + kTouchWaves)) void k_bat
     const int i = lane + 64 * r;
     y[r] = i < m ? zb[c * m + i] : 0.0;
   }
-  wave_apply_solve<RPL>(m, n, fact, tau, y);
+  wave_apply_solve<RPL, false>(m, n, fact, tau, y);
   // X += dx, with both norms
   double dx2 = 0.0, x2 = 0.0;
 #pragma unroll
@@ -1157,7 +1160,7 @@ __global__ __launch_bounds__(64 * as_waves(RPL)) void k_qr_apply_solve_reg(int m
       const int i = lane + 64 * r;
       y[r] = i < m ? Bm[i + (int64_t)c * m] : 0.0;
     }
-    wave_apply_solve<RPL>(m, n, fact, tau, y);
+    wave_apply_solve<RPL, true>(m, n, fact, tau, y);
 #pragma unroll
     for (int r = 0; r < RPL; ++r) {
       const int i = lane + 64 * r;

@@ -409,3 +409,24 @@ def test_refinement_fixed_point_shapes(ms, d, n, nrhs, k2):
     # size of x plus that of b over A, kappa(Z_A) below 60 for every shape here
     scale = X0.norm().item() + B.norm().item() / np.sqrt(d)
     assert (X1 - X0).norm().item() <= 60 * max(n, 10) * k2 * 2.0 ** -53 * scale * 10
+
+
+# A reflector with tau = 0 (S A is already triangular) leaves an infinite sketched
+# residual as it is, and an infinite numerator over R's diagonal is infinite: a finite x
+# whose residual overflows in one row becomes infinite and not NaN.  Exact: G S A
+# is zero below its first entry, and G's entries are powers of two.
+def test_refinement_identity_reflector_keeps_infinity(ms):
+    print("refine tau=0", flush=True)
+    big = 1.5 * 2.0 ** 1023
+    A = np.array([[1.0], [-1.0], [0.0], [0.0]])
+    B = np.array([[big], [big], [0.0], [0.0]])
+    G = np.full((4, 4), 2.0 ** -9)
+    G[0, 0], G[0, 1] = 2.0 ** -20, -2.0 ** -10
+    h, s = np.arange(4, dtype=np.int32), np.ones(4, dtype=np.int8)
+    args = (to_dev(A), to_dev(B), to_dev(h), to_dev(s), to_dev(G), 4)
+    X0, ws0 = ms.sketch_lstsq(*args)
+    ms.check_status(ws0)
+    assert np.isfinite(to_host(X0)).all()
+    X1, ws1 = ms.sketch_lstsq(*args, refine_steps=1)
+    ms.check_status(ws1)
+    assert np.isposinf(to_host(X1)).all()
