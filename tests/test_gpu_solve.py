@@ -411,6 +411,21 @@ def test_refinement_fixed_point_shapes(ms, d, n, nrhs, k2):
     assert (X1 - X0).norm().item() <= 60 * max(n, 10) * k2 * 2.0 ** -53 * scale * 10
 
 
+# The (split, tile) items dealt to the dies: fewer items than dies, one more than a
+# multiple of eight, one split of many tiles, and many splits of an odd tile count.
+# Bar as above.
+@pytest.mark.parametrize("k2,k,nc", [(5, 7, 40), (130, 20, 150), (1100, 100, 130), (2050, 3, 300),
+                                     (16, 40000, 290), (129, 9000, 400), (300, 5000, 700)])
+def test_gaussian_f64_items(ms, k2, k, nc):
+    print("gaussian f64 items k2=%d k=%d nc=%d" % (k2, k, nc), flush=True)
+    rng = np.random.default_rng(k2 + k + nc)
+    G, Y = rng.standard_normal((k2, k)), rng.standard_normal((k, nc))
+    Z, ws = ms.gaussian_apply(to_dev(G), to_dev(Y))
+    ms.check_status(ws)
+    err = np.abs(to_host(Z) - G @ Y)
+    assert np.all(err <= 2 * (k + 256) * 2.0 ** -53 * (np.abs(G) @ np.abs(Y)))
+
+
 # A reflector with tau = 0 (S A is already triangular) leaves an infinite sketched
 # residual as it is, and an infinite numerator over R's diagonal is infinite: a finite x
 # whose residual overflows in one row becomes infinite and not NaN.  Exact: G S A

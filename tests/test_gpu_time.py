@@ -1,0 +1,63 @@
+"""Times of calls that differ in one property, on the GPU: a shape, a row count or a
+bucket map that is served by a rule of its own must not cost far more than its
+neighbour.  Every bar is on the ratio of two times of the same process, well
+above what was measured and well below what the fault that it guards against
+cost.
+"""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ms():
+    import paper_2508_14209_amd as ms
+    return ms
+
+
+def _us(fn, reps=12):
+    """Least time of a call on the GPU, in microseconds."""
+    fn()
+    torch.cuda.synchronize()
+    ev = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True))
+          for _ in range(reps)]
+    for a, b in ev:
+        a.record()
+        fn()
+        b.record()
+    torch.cuda.synchronize()
+    return 1e3 * min(a.elapsed_time(b) for a, b in ev)
+
+
+def _gen(seed):
+    return torch.Generator(device="cuda").manual_seed(seed)
+
+
+def _normal(rows, cols, dtype=torch.float64, seed=0):
+    return torch.randn((cols, rows), generator=_gen(seed), device="cuda", dtype=dtype).t()
+
+
+def _gaussian(ms, k2, k, n):
+    G, Y = _normal(k2, k), _normal(k, n, seed=1)
+    Z = ms.empty_colmajor(k2, n, torch.float64)
+    ws = ms.workspace(ms.workspace_size("gaussian", n=n, k=k, k2=k2))
+    us = _us(lambda: ms.gaussian_apply(G, Y, Z=Z, ws=ws))
+    print("gaussian k2=%d k=%d n=%d: %.1f us" % (k2, k, n, us), flush=True)
+    return us
+
+
+# FP64 product: two column tiles fill the chip evenly, three do not divide it (1.17 times
+# the columns took 2.1 times the time when a die got whole splits only).
+def test_gaussian_f64_three_tiles(ms):
+    assert _gaussian(ms, 16, 131072, 300) <= 1.6 * _gaussian(ms, 16, 131072, 257)
+
+
+# ... and one split of many tiles has the whole chip too: no more than eight copies of the result
+# (it takes 4.4; on one die alone it took 13.7).
+def test_gaussian_f64_one_split(ms):
+    src, dst = _normal(4096, 2000), ms.empty_colmajor(4096, 2000, torch.float64)
+    copy = _us(lambda: dst.copy_(src))
+    print("copy: %.1f us" % copy, flush=True)
+    assert _gaussian(ms, 4096, 16, 2000) <= 8 * copy
