@@ -615,11 +615,12 @@ __global__ __launch_bounds__(kDThreads, 2) void k_gemm_f64(int M, int N, int64_t
   // staging: G tasks q (k = tid / 64 + 8 q of the slab, rows 2 (tid % 64) and
   // the next one), Y tasks q (slot tid + 512 q).  A row pair past M reads the
   // last pair and a column past N the last column: their products are not
-  // stored (M odd: the last row sits second in the pair read for it).
+  // stored (M odd: the last row sits second in the pair read for it; M = 1: what
+  // follows the row in memory, up to the last k, sits second).
   constexpr int QY = (NB * 256 + kDThreads - 1) / kDThreads;
   v2d ga[4], ya[QY];
   const int grow = m0 + 2 * lane;
-  const bool lastrow = grow == M - 1;
+  const bool lastrow = M > 1 && grow == M - 1;
   const double *gp = G + max(0, min(grow, M - 2)) + (kb + wave) * ldg;
   const double *yp[QY];
   const int yk = 8 * ((tid >> 6) & 3) + 2 * ((tid >> 4) & 3);   // k within the slab
@@ -699,8 +700,10 @@ __global__ __launch_bounds__(kDThreads, 2) void k_gemm_f64(int M, int N, int64_t
       for (int j = 0; j < NB; ++j) b[j] = nb[j];
     }
   };
-  // whole slabs, then the part of one that may be left (M = 1: every slab)
-  const int64_t whole = M >= 2 ? klen / kDKS * kDKS : 0;
+  // whole slabs, then the part of one that may be left (M = 1: the slab that holds the
+  // last k too, whose pair would end past G; every slab guarded, 131,072 x 1000 took
+  // 1340 us against 310)
+  const int64_t whole = (M == 1 && ke == K ? klen - 1 : klen) / kDKS * kDKS;
   int cur = 0;
   if (whole > 0) {
     fetch(0);

@@ -426,6 +426,24 @@ def test_gaussian_f64_items(ms, k2, k, nc):
     assert np.all(err <= 2 * (k + 256) * 2.0 ** -53 * (np.abs(G) @ np.abs(Y)))
 
 
+# One row: K below, at and past a slab and several splits (the last slab is
+# guarded, its last pair would end past G), leading dimension 1 and 3, NaN in the padding
+# that a pair reads.  Bar as above.
+@pytest.mark.parametrize("k", [31, 32, 33, 64, 128, 4096, 4097, 131072])
+@pytest.mark.parametrize("pad", [0, 2])
+def test_gaussian_f64_one_row(ms, k, pad):
+    nc = 35
+    print("gaussian f64 one row k=%d pad=%d" % (k, pad), flush=True)
+    rng = np.random.default_rng(k)
+    G, Y = rng.standard_normal((1, k)), rng.standard_normal((k, nc))
+    buf = torch.full((k, 1 + pad), float("nan"), dtype=torch.float64, device="cuda")
+    buf[:, 0] = torch.from_numpy(G[0]).cuda()
+    Z, ws = ms.gaussian_apply(buf.t()[:1], to_dev(Y))
+    ms.check_status(ws)
+    err = np.abs(to_host(Z) - G @ Y)
+    assert np.all(err <= 2 * (k + 256) * 2.0 ** -53 * (np.abs(G) @ np.abs(Y)))
+
+
 # A reflector with tau = 0 (S A is already triangular) leaves an infinite sketched
 # residual as it is, and an infinite numerator over R's diagonal is infinite: a finite x
 # whose residual overflows in one row becomes infinite and not NaN.  Exact: G S A

@@ -61,3 +61,8 @@ def test_gaussian_f64_one_split(ms):
     copy = _us(lambda: dst.copy_(src))
     print("copy: %.1f us" % copy, flush=True)
     assert _gaussian(ms, 4096, 16, 2000) <= 8 * copy
+
+
+# ... and one row costs no more than two (2.2 times when its slabs were all guarded).
+def test_gaussian_f64_one_row(ms):
+    assert _gaussian(ms, 1, 131072, 500) <= 1.5 * _gaussian(ms, 2, 131072, 500)
