@@ -16,28 +16,31 @@
 
 namespace ms {
 
-// Four consecutive rows of a column.  The vector loads are aligned to the
-// element only (a dword-aligned multi-dword global load is legal on CDNA), so
-// a column may start at any element.
-template <typename TA>
-__device__ __forceinline__ auto rows4_nt(const TA *p) {
+// Four consecutive rows of a column, NT: by a nontemporal load.  The loads are
+// aligned to the element only (a dword-aligned multi-dword global load is legal on
+// CDNA), so a column may start at any element.
+template <bool NT, typename TA>
+__device__ __forceinline__ auto rows4(const TA *p) {
   typedef TA V __attribute__((ext_vector_type(4)));
   typedef TA Vu __attribute__((ext_vector_type(4), aligned(sizeof(TA))));
-  return (V)__builtin_nontemporal_load((const __attribute__((address_space(1))) Vu *)p);
+  const auto *g = (const __attribute__((address_space(1))) Vu *)p;
+  return NT ? (V)__builtin_nontemporal_load(g) : (V)*g;
 }
 
 constexpr int kResXlds = 8192;  // most doubles of X staged in LDS (64 KB)
 
-// The residuals of V groups of four rows, i0 + v * vstep each, every row inside
-// the matrix.  x(j, c): X[j, c].  U columns' loads are issued before their
-// products.
-template <typename TA, int RH, int V, typename XF>
-__device__ __forceinline__ void residual_groups(int64_t i0, int64_t vstep, int n, int nrhs,
-                                                const TA *__restrict__ A, int64_t lda,
+// The residuals of V groups of four rows, i0 + v * vstep each.  Unless LAST every
+// row is inside the matrix; LAST (V = 1, d >= 4): the group that would end past row d
+// starts at d - 4 instead and stores the rows that are its own.  x(j, c): X[j, c].
+// U columns' loads are issued before their products.
+template <typename TA, int RH, int V, int U, bool NT, bool LAST, typename XF>
+__device__ __forceinline__ void residual_groups(int64_t i0, int64_t vstep, int64_t d, int n,
+                                                int nrhs, const TA *__restrict__ A, int64_t lda,
                                                 const TA *__restrict__ B, int64_t ldb, const XF &x,
                                                 double *__restrict__ r, int64_t ldr) {
+  static_assert(!LAST || V == 1, "one group");
+  const int64_t g0 = LAST ? min(i0, d - 4) : i0;
   typedef TA V4 __attribute__((ext_vector_type(4)));
-  constexpr int U = 2;
   double acc[V][4][RH];
 #pragma unroll
   for (int v = 0; v < V; ++v)
@@ -61,14 +64,15 @@ __device__ __forceinline__ void residual_groups(int64_t i0, int64_t vstep, int n
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int v = 0; v < V; ++v) a[u][v] = rows4_nt(A + i0 + v * vstep + (int64_t)(j + u) * lda);
+      for (int v = 0; v < V; ++v) a[u][v] = rows4<NT>(A + g0 + v * vstep + (int64_t)(j + u) * lda);
+    if (LAST) __builtin_amdgcn_sched_barrier(0);   // all of them, or the compiler puts some off
 #pragma unroll
     for (int u = 0; u < U; ++u) column(j + u, a[u]);
   }
   for (; j < n; ++j) {
     V4 a[V];
 #pragma unroll
-    for (int v = 0; v < V; ++v) a[v] = rows4_nt(A + i0 + v * vstep + (int64_t)j * lda);
+    for (int v = 0; v < V; ++v) a[v] = rows4<NT>(A + g0 + v * vstep + (int64_t)j * lda);
     column(j, a);
   }
 #pragma unroll
@@ -76,28 +80,38 @@ __device__ __forceinline__ void residual_groups(int64_t i0, int64_t vstep, int n
     if (c < nrhs) {
 #pragma unroll
       for (int v = 0; v < V; ++v) {
-        const V4 b = rows4_nt(B + i0 + v * vstep + (int64_t)c * ldb);
+        const V4 b = rows4<NT>(B + g0 + v * vstep + (int64_t)c * ldb);
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-          r[i0 + v * vstep + q + (int64_t)c * ldr] = (double)b[q] - acc[v][q][c];
+          if (!LAST || g0 + q >= i0)
+            r[g0 + v * vstep + q + (int64_t)c * ldr] = (double)b[q] - acc[v][q][c];
       }
     }
 }
 
-// One row's residuals, element by element (the rows past the last whole group).
-template <typename TA, typename XF>
-__device__ __forceinline__ void residual_row(int64_t i, int n, int nrhs, const TA *__restrict__ A,
-                                             int64_t lda, const TA *__restrict__ B, int64_t ldb,
-                                             const XF &x, double *__restrict__ r, int64_t ldr) {
-  for (int c = 0; c < nrhs; ++c) {
-    double acc = 0.0;
-    for (int j = 0; j < n; ++j) acc += (double)gload(A + i + (int64_t)j * lda) * x(j, c);
-    r[i + (int64_t)c * ldr] = (double)gload(B + i + (int64_t)c * ldb) - acc;
+// The residuals of a matrix of fewer than four rows, a row per thread.
+template <typename TA, int RH, typename XF>
+__device__ __forceinline__ void residual_rows(int64_t d, int n, int nrhs, const TA *__restrict__ A,
+                                              int64_t lda, const TA *__restrict__ B, int64_t ldb,
+                                              const XF &x, double *__restrict__ r, int64_t ldr) {
+  const int64_t i = threadIdx.x;
+  if (i >= d) return;
+  double acc[RH];
+#pragma unroll
+  for (int c = 0; c < RH; ++c) acc[c] = 0.0;
+#pragma unroll 4
+  for (int j = 0; j < n; ++j) {
+    const double a = (double)gload(A + i + (int64_t)j * lda);
+#pragma unroll
+    for (int c = 0; c < RH; ++c) acc[c] += a * x(j, c);
   }
+#pragma unroll
+  for (int c = 0; c < RH; ++c)
+    if (c < nrhs) r[i + (int64_t)c * ldr] = (double)gload(B + i + (int64_t)c * ldb) - acc[c];
 }
 
 // RH: right-hand sides held (nrhs <= RH; the X of the missing ones is zero).
-template <typename TA, bool XLDS, int RH, int T, int V>
+template <typename TA, bool XLDS, int RH, int T, int V, bool NT>
 __global__ __launch_bounds__(T) void k_residual(int64_t d, int n, int nrhs,
                                                 const TA *__restrict__ A, int64_t lda,
                                                 const TA *__restrict__ B, int64_t ldb,
@@ -115,18 +129,17 @@ __global__ __launch_bounds__(T) void k_residual(int64_t d, int n, int nrhs,
     return XLDS ? xs[j * RH + c] : c < nrhs ? X[j + (int64_t)c * ldx] : 0.0;
   };
   constexpr int64_t blk = (int64_t)4 * T * V;
+  constexpr int U = 2;
   int64_t r0 = (int64_t)blockIdx.x * blk;
   for (; r0 + blk <= d; r0 += gridDim.x * blk)
-    residual_groups<TA, RH, V>(r0 + 4 * (int64_t)threadIdx.x, 4 * T, n, nrhs, A, lda, B, ldb, xv, r,
-                               ldr);
-  if (r0 < d) {   // the last rows: whole groups one at a time, then single rows
-    for (int64_t i = r0 + 4 * (int64_t)threadIdx.x; i < d; i += 4 * T) {
-      if (i + 4 <= d)
-        residual_groups<TA, RH, 1>(i, 0, n, nrhs, A, lda, B, ldb, xv, r, ldr);
-      else
-        for (int64_t q = i; q < d; ++q) residual_row(q, n, nrhs, A, lda, B, ldb, xv, r, ldr);
-    }
-  }
+    residual_groups<TA, RH, V, U, NT, false>(r0 + 4 * (int64_t)threadIdx.x, 4 * T, d, n, nrhs, A,
+                                             lda, B, ldb, xv, r, ldr);
+  // the last rows a group at a time (the matrix's last one to three row by row in one
+  // lane, each element read for every right-hand side, were a chain of up to 3 n nrhs
+  // loads: a step of 100,003 x 256 FP32, 8 right-hand sides, 840 us, now 390)
+  if (r0 < d && d < 4) return residual_rows<TA, RH>(d, n, nrhs, A, lda, B, ldb, xv, r, ldr);
+  for (int64_t i = r0 + 4 * (int64_t)threadIdx.x; i < d; i += 4 * T)
+    residual_groups<TA, RH, 1, 4, false, true>(i, 0, d, n, nrhs, A, lda, B, ldb, xv, r, ldr);
 }
 
 template <typename TA, bool XLDS, int RH, int T, int V>
@@ -134,7 +147,7 @@ static void launch_residual_k(unsigned grid, int64_t d, int64_t n, int64_t nrhs,
                               int64_t lda, const TA *B, int64_t ldb, const double *X, int64_t ldx,
                               double *r, int64_t ldr, hipStream_t st) {
   const size_t lds = XLDS ? (size_t)n * RH * sizeof(double) : 0;
-  hipLaunchKernelGGL((k_residual<TA, XLDS, RH, T, V>), dim3(grid), dim3(T), lds, st, d, (int)n,
+  hipLaunchKernelGGL((k_residual<TA, XLDS, RH, T, V, true>), dim3(grid), dim3(T), lds, st, d, (int)n,
                      (int)nrhs, A, lda, B, ldb, X, ldx, r, ldr);
 }
 
@@ -191,6 +204,7 @@ __global__ __launch_bounds__(256) void k_batch_residual(
     int count, const ms_problem *__restrict__ P, const BatchEntry *__restrict__ E,
     const BatchTotals *__restrict__ tot, unsigned char *__restrict__ rarea) {
   constexpr int RH = kBatchMaxRefineRhs;
+  constexpr bool NT = true;
   static_assert(kBatchResRows == 2048, "256 threads, two groups of four rows each");
   __shared__ __align__(16) double xs[kBatchMaxCols * RH];  // xs[j * rh + c] = X[j, c]
   const int64_t total = tot->res_items;
@@ -218,14 +232,14 @@ __global__ __launch_bounds__(256) void k_batch_residual(
     auto xv = [&](int j, int c) { return xs[j * RH_ + c]; };                                    \
     if (whole) {                                                                                \
       for (int v = 0; v < 2; v += V_)                                                           \
-        residual_groups<TA, RH_, V_>(i0 + 1024 * v, 1024, n, nrhs, A, lda, B, ldb, xv, r, d);   \
+        residual_groups<TA, RH_, V_, 2, NT, false>(i0 + 1024 * v, 1024, d, n, nrhs, A, lda, B,  \
+                                                   ldb, xv, r, d);                              \
+    } else if (d >= 4) {                                                                        \
+      for (int64_t i = i0; i < d; i += 1024)                                                    \
+        residual_groups<TA, RH_, 1, 4, false, true>(i, 0, d, n, nrhs, A, lda, B, ldb, xv, r,    \
+                                                    d);                                         \
     } else {                                                                                    \
-      for (int64_t i = i0; i < d; i += 1024) {                                                  \
-        if (i + 4 <= d)                                                                         \
-          residual_groups<TA, RH_, 1>(i, 0, n, nrhs, A, lda, B, ldb, xv, r, d);                 \
-        else                                                                                    \
-          for (int64_t q = i; q < d; ++q) residual_row(q, n, nrhs, A, lda, B, ldb, xv, r, d);   \
-      }                                                                                         \
+      residual_rows<TA, RH_>(d, n, nrhs, A, lda, B, ldb, xv, r, d);                             \
     }                                                                                           \
   }
     if (rh == 1)

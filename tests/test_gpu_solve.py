@@ -463,3 +463,36 @@ def test_refinement_identity_reflector_keeps_infinity(ms):
     X1, ws1 = ms.sketch_lstsq(*args, refine_steps=1)
     ms.check_status(ws1)
     assert np.isposinf(to_host(X1)).all()
+
+
+# The residual's last rows: row counts of every remainder of a group of four, fewer than
+# four rows, and a few rows past the thresholds of the wide workgroups.  The same matrix with zero
+# rows up to whole workgroups sends every row through the other path; in the
+# deterministic mode a zero row adds +0.0 to its bucket, so that sketch, factors,
+# residuals and their sketches keep their bits, and X with them.
+@pytest.mark.parametrize("d,n,nrhs", [(1, 1, 1), (2, 2, 3), (3, 1, 8), (4, 2, 5), (5, 3, 1),
+                                      (1025, 9, 4), (4098, 17, 8), (10003, 40, 2),
+                                      (4194304 + 16385, 3, 1), (2097152 + 3, 2, 2),
+                                      (2097152 + 2050, 2, 4), (1048576 + 4099, 2, 8)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_refinement_last_rows(ms, d, n, nrhs, dtype):
+    print("refine last rows d=%d n=%d nrhs=%d %s" % (d, n, nrhs, dtype), flush=True)
+    k, k2 = 4096, 2 * n + 1
+    full = (d + 16383) // 16384 * 16384
+    g = torch.Generator(device="cuda").manual_seed(d + n)
+    A = torch.zeros((n, full), device="cuda", dtype=dtype)
+    B = torch.zeros((nrhs, full), device="cuda", dtype=dtype)
+    A[:, :d] = torch.randn((n, d), generator=g, device="cuda", dtype=dtype)
+    B[:, :d] = torch.randn((nrhs, d), generator=g, device="cuda", dtype=dtype)
+    # a bucket each while there are few rows, so that S A keeps A's rank
+    h = torch.randint(0, k, (full,), generator=g, device="cuda", dtype=torch.int32)
+    h[:8] = torch.arange(8, device="cuda")
+    s = torch.randint(0, 2, (full,), generator=g, device="cuda", dtype=torch.int8) * 2 - 1
+    G = (torch.randn((k, k2), generator=g, device="cuda", dtype=dtype) / k2 ** 0.5).t()
+    A, B = A.t(), B.t()
+    X, ws = ms.sketch_lstsq(A[:d], B[:d], h[:d].contiguous(), s[:d].contiguous(), G, k,
+                            mode="sorted", refine_steps=2)
+    ms.check_status(ws)
+    X0, ws0 = ms.sketch_lstsq(A, B, h, s, G, k, mode="sorted", refine_steps=2)
+    ms.check_status(ws0)
+    assert torch.isfinite(X).all() and torch.equal(X, X0)

@@ -66,3 +66,25 @@ def test_gaussian_f64_one_split(ms):
 # ... and one row costs no more than two (2.2 times when its slabs were all guarded).
 def test_gaussian_f64_one_row(ms):
     assert _gaussian(ms, 1, 131072, 500) <= 1.5 * _gaussian(ms, 2, 131072, 500)
+
+
+def _lstsq(ms, d, n, nrhs, k, k2, dtype, refine, mode="auto"):
+    A, B = _normal(d, n, dtype), _normal(d, nrhs, dtype, seed=1)
+    h = torch.randint(0, k, (d,), generator=_gen(2), dtype=torch.int32, device="cuda")
+    s = torch.randint(0, 2, (d,), generator=_gen(3), dtype=torch.int8, device="cuda") * 2 - 1
+    G = _normal(k2, k, dtype, seed=4)
+    X = ms.empty_colmajor(n, nrhs, torch.float64)
+    dt = ms.MS_F64 if dtype == torch.float64 else ms.MS_F32
+    ws = ms.workspace(ms.workspace_size("lstsq", d=d, n=n, nrhs=nrhs, k=k, k2=k2, a_dtype=dt,
+                                        g_dtype=dt, mode=mode, refine_steps=refine))
+    us = _us(lambda: ms.sketch_lstsq(A, B, h, s, G, k, mode=mode, refine_steps=refine, X=X, ws=ws))
+    print("lstsq d=%d n=%d nrhs=%d refine=%d: %.1f us" % (d, n, nrhs, refine, us), flush=True)
+    return us
+
+
+# The last one to three rows of a refinement's residual: a row count that is no multiple of
+# four costs what its neighbour costs (1.6 to 2.1 times when they were one lane's chain).
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_refinement_odd_rows(ms, dtype):
+    args = (256, 8, 1024, 256, dtype, 8)
+    assert _lstsq(ms, 100003, *args) <= 1.25 * _lstsq(ms, 100000, *args)
