@@ -29,6 +29,14 @@ __device__ __forceinline__ auto rows4(const TA *p) {
 
 constexpr int kResXlds = 8192;  // most doubles of X staged in LDS (64 KB)
 
+// FP32 data of more than the last-level cache's 256 MB is read by nontemporal loads,
+// all else by ordinary ones: a solve reads A and B for the sketch and for each step,
+// and what is cached stays so.  Eight steps, FP32: 600,000 x 128 (302 MB), 4 right-hand sides
+// 1.46 ms cached, 1.41 nontemporal; 2,000,000 x 16 (153 MB) 0.70 and 0.77.  FP64:
+// cached is as fast or faster at every size measured (3 to 8450 MB), 2,000,000 x 8,
+// 1 right-hand side 0.51 and 0.58 ms, 4,194,304 x 256, 2 right-hand sides 14.2 and 14.4.
+constexpr int64_t kResCached = (int64_t)256 << 20;
+
 // The residuals of V groups of four rows, i0 + v * vstep each.  Unless LAST every
 // row is inside the matrix; LAST (V = 1, d >= 4): the group that would end past row d
 // starts at d - 4 instead and stores the rows that are its own.  x(j, c): X[j, c].
@@ -65,7 +73,7 @@ __device__ __forceinline__ void residual_groups(int64_t i0, int64_t vstep, int64
     for (int u = 0; u < U; ++u)
 #pragma unroll
       for (int v = 0; v < V; ++v) a[u][v] = rows4<NT>(A + g0 + v * vstep + (int64_t)(j + u) * lda);
-    if (LAST) __builtin_amdgcn_sched_barrier(0);   // all of them, or the compiler puts some off
+    __builtin_amdgcn_sched_barrier(0);   // all of them, or the compiler may put some off
 #pragma unroll
     for (int u = 0; u < U; ++u) column(j + u, a[u]);
   }
@@ -129,14 +137,15 @@ __global__ __launch_bounds__(T) void k_residual(int64_t d, int n, int nrhs,
     return XLDS ? xs[j * RH + c] : c < nrhs ? X[j + (int64_t)c * ldx] : 0.0;
   };
   constexpr int64_t blk = (int64_t)4 * T * V;
-  constexpr int U = 2;
+  constexpr int U = V > 1 || (RH == 8 && sizeof(TA) == 8) ? 2 : 4;   // in flight, as the registers allow
   int64_t r0 = (int64_t)blockIdx.x * blk;
   for (; r0 + blk <= d; r0 += gridDim.x * blk)
     residual_groups<TA, RH, V, U, NT, false>(r0 + 4 * (int64_t)threadIdx.x, 4 * T, d, n, nrhs, A,
                                              lda, B, ldb, xv, r, ldr);
   // the last rows a group at a time (the matrix's last one to three row by row in one
   // lane, each element read for every right-hand side, were a chain of up to 3 n nrhs
-  // loads: a step of 100,003 x 256 FP32, 8 right-hand sides, 840 us, now 390)
+  // loads: eight steps of 100,003 x 256 FP32, 8 right-hand sides, with the solve 6.7 ms,
+  // now 2.6)
   if (r0 < d && d < 4) return residual_rows<TA, RH>(d, n, nrhs, A, lda, B, ldb, xv, r, ldr);
   for (int64_t i = r0 + 4 * (int64_t)threadIdx.x; i < d; i += 4 * T)
     residual_groups<TA, RH, 1, 4, false, true>(i, 0, d, n, nrhs, A, lda, B, ldb, xv, r, ldr);
@@ -147,8 +156,12 @@ static void launch_residual_k(unsigned grid, int64_t d, int64_t n, int64_t nrhs,
                               int64_t lda, const TA *B, int64_t ldb, const double *X, int64_t ldx,
                               double *r, int64_t ldr, hipStream_t st) {
   const size_t lds = XLDS ? (size_t)n * RH * sizeof(double) : 0;
-  hipLaunchKernelGGL((k_residual<TA, XLDS, RH, T, V, true>), dim3(grid), dim3(T), lds, st, d, (int)n,
-                     (int)nrhs, A, lda, B, ldb, X, ldx, r, ldr);
+  if (sizeof(TA) == 4 && d * (n + nrhs) * 4 > kResCached)
+    hipLaunchKernelGGL((k_residual<TA, XLDS, RH, T, V, sizeof(TA) == 4>), dim3(grid), dim3(T), lds,
+                       st, d, (int)n, (int)nrhs, A, lda, B, ldb, X, ldx, r, ldr);
+  else
+    hipLaunchKernelGGL((k_residual<TA, XLDS, RH, T, V, false>), dim3(grid), dim3(T), lds, st, d,
+                       (int)n, (int)nrhs, A, lda, B, ldb, X, ldx, r, ldr);
 }
 
 // T, V: the workgroup of this many right-hand sides when d gives every compute
@@ -204,7 +217,7 @@ __global__ __launch_bounds__(256) void k_batch_residual(
     int count, const ms_problem *__restrict__ P, const BatchEntry *__restrict__ E,
     const BatchTotals *__restrict__ tot, unsigned char *__restrict__ rarea) {
   constexpr int RH = kBatchMaxRefineRhs;
-  constexpr bool NT = true;
+  constexpr bool NT = sizeof(TA) == 4;   // (a batch is mostly more than the cache holds)
   static_assert(kBatchResRows == 2048, "256 threads, two groups of four rows each");
   __shared__ __align__(16) double xs[kBatchMaxCols * RH];  // xs[j * rh + c] = X[j, c]
   const int64_t total = tot->res_items;

@@ -88,3 +88,10 @@ def _lstsq(ms, d, n, nrhs, k, k2, dtype, refine, mode="auto"):
 def test_refinement_odd_rows(ms, dtype):
     args = (256, 8, 1024, 256, dtype, 8)
     assert _lstsq(ms, 100003, *args) <= 1.25 * _lstsq(ms, 100000, *args)
+
+
+# ... also one row past whole workgroups of the widest kind (7 % of eight steps when its
+# loads went past the caches and one after another).
+def test_refinement_one_row_more(ms):
+    args = (256, 1, 1024, 256, torch.float64, 8)
+    assert _lstsq(ms, 4194305, *args) <= 1.06 * _lstsq(ms, 4194304, *args)
