@@ -164,15 +164,18 @@ static void launch_residual_k(unsigned grid, int64_t d, int64_t n, int64_t nrhs,
                        (int)n, (int)nrhs, A, lda, B, ldb, X, ldx, r, ldr);
 }
 
-// T, V: the workgroup of this many right-hand sides when d gives every compute
-// unit one (32 V T bytes of FP64, 16 V T of FP32 of a column at a time, as many
-// as the registers of the sums allow); fewer rows take 1024 at a time.
+// T, V: the wide workgroup of this many right-hand sides, one to a compute unit (32 V T
+// bytes of FP64, 16 V T of FP32 of a column at a time, as many as the registers of
+// the sums allow), where its rounds are at least five sixths full; else 1024 rows at a
+// time.  Eight steps, 1 right-hand side: 7,000,000 x 64 (0.83 full) FP64 6.23 ms wide, 6.43
+// narrow, 9,000,000 (0.72) 8.6 and 8.1, 4,300,000 (0.51) 5.1 and 4.1 (FP32 3.48 and 3.52,
+// 4.65 and 4.46, 2.75 and 2.35).
 template <typename TA, int RH, int T, int V>
 static hipError_t launch_residual_rh(int64_t d, int64_t n, int64_t nrhs, const TA *A, int64_t lda,
                                      const TA *B, int64_t ldb, const double *X, int64_t ldx,
                                      double *r, int64_t ldr, hipStream_t st) {
-  const int64_t cus = dev_info().cus;
-  const bool wide = d >= cus * 4 * T * V, xl = n * RH <= kResXlds;
+  const int64_t cus = dev_info().cus, round = cus * 4 * T * V;
+  const bool wide = 6 * d >= 5 * round * ((d + round - 1) / round), xl = n * RH <= kResXlds;
   const unsigned gw = (unsigned)std::min<int64_t>((d + 4 * T * V - 1) / (4 * T * V), cus * (1024 / T));
   const unsigned gn = (unsigned)std::min<int64_t>((d + 1023) / 1024, cus * 8);
   if (wide && xl)

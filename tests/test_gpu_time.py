@@ -95,3 +95,10 @@ def test_refinement_odd_rows(ms, dtype):
 def test_refinement_one_row_more(ms):
     args = (256, 1, 1024, 256, torch.float64, 8)
     assert _lstsq(ms, 4194305, *args) <= 1.06 * _lstsq(ms, 4194304, *args)
+
+
+# 2.5 % more rows than one round of the widest workgroups: a second, nearly empty round took half as
+# long again.
+def test_refinement_nearly_empty_round(ms):
+    args = (64, 1, 256, 64, torch.float64, 8)
+    assert _lstsq(ms, 4300000, *args) <= 1.2 * _lstsq(ms, 4194304, *args)
