@@ -110,10 +110,20 @@ constexpr int kBfCountMaxRun = 64;
 // one thread.  A block is stored, in the 16 KB its 32-bit keys would take, as
 // 4096 16-bit entries in (bucket, row) order -- bucket within its slice |
 // row << 3 | sign << 15 -- followed by the slices' end positions (16 bits each).
+// A block in which one bucket has many more rows than the average keeps its 32-bit
+// keys, for bf_fold_uneven, whose threads share out positions: the walk of a slice is
+// a serial chain.  Bit 30 of the first word of the block's second half tells: clear in two
+// end positions, set in such a block's key there (kBfPad has it set).
 constexpr int kBfSlices = 4096;
 constexpr int kBfSliceMinK = 32;
+constexpr uint32_t kBfUneven = 0x40000000u;
 constexpr int bf_slice_buckets(int64_t k) {
   return k <= kBfSlices ? 1 : k <= 2 * kBfSlices ? 2 : 4;
+}
+// The most rows of a bucket in a block that is walked; uniformly hashed rows exceed it in
+// about one block in ten thousand.
+__device__ __forceinline__ uint32_t bf_even_rows(int k) {
+  return 2 * (kBfRows / k) + (k <= kBfSlices ? 14 : k <= 2 * kBfSlices ? 11 : 8);
 }
 
 size_t bf_count_lds(int64_t k) { return (size_t)(k + 1 + 3) / 4 * 16 + (size_t)kBfRows * 4; }
@@ -125,14 +135,14 @@ __global__ __launch_bounds__(kBfT) void k_bf_keys_count(int64_t d, int k,
                                                         uint32_t *__restrict__ keys, int *status) {
   extern __shared__ __align__(16) uint32_t bsm[];
   __shared__ uint32_t wsum[kBfT / 64];
-  __shared__ int s_long;
+  __shared__ int s_long, s_uneven;
   uint32_t *cnt = bsm;                              // k + 1 counters
   uint32_t *key = bsm + (k + 1 + 3) / 4 * 4;        // kBfRows keys, 16-byte aligned
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int64_t r0 = (int64_t)blockIdx.x * kBfRows;
   const bool vec = (((uintptr_t)h & 15) | ((uintptr_t)s & 3)) == 0;
   for (int m = tid; m <= k; m += kBfT) cnt[m] = 0;
-  if (tid == 0) s_long = 0;
+  if (tid == 0) s_long = s_uneven = 0;
   bool bad = false;
   uint32_t v[4];
   bf_make_keys(d, k, h, s, r0, vec, v, bad);
@@ -144,12 +154,14 @@ __global__ __launch_bounds__(kBfT) void k_bf_keys_count(int64_t d, int k,
   __syncthreads();
   // exclusive scan of the k + 1 counts, thread t owning a contiguous range
   const int per = (k + 1 + kBfT - 1) / kBfT;
+  const uint32_t most = bf_even_rows(k);
   uint32_t loc = 0;
   for (int q = 0; q < per; ++q) {
     const int m = tid * per + q;
     if (m <= k) {
       loc += cnt[m];
       if (cnt[m] > (uint32_t)kBfCountMaxRun && m < k) atomicOr(&s_long, 1);
+      if (SLICED && cnt[m] > most && m < k) s_uneven = 1;
     }
   }
   uint32_t incl = loc;
@@ -163,14 +175,16 @@ __global__ __launch_bounds__(kBfT) void k_bf_keys_count(int64_t d, int k,
   const bool longrun = s_long != 0;
   // thread t's sorted keys 4t .. 4t + 3, as keys or as 16-bit entries
   const int nb = SLICED ? bf_slice_buckets(k) : 1;
+  const bool sliced = SLICED && !s_uneven;
   auto store = [&]() {
-    if (SLICED) {
+    if (sliced) {
       uint32_t e[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q)
         e[q] = (bf_bucket(v[q]) & (uint32_t)(nb - 1)) | (v[q] & 0xfffu) << 3 | (v[q] >> 31) << 15;
       *reinterpret_cast<uint2 *>(keys + r0 + 2 * tid) = make_uint2(e[0] | e[1] << 16, e[2] | e[3] << 16);
     } else {
+      if (SLICED && tid == kBfRows / 2 / 4) v[0] |= kBfUneven;
       *reinterpret_cast<uint4 *>(keys + r0 + 4 * tid) = make_uint4(v[0], v[1], v[2], v[3]);
     }
   };
@@ -194,7 +208,8 @@ __global__ __launch_bounds__(kBfT) void k_bf_keys_count(int64_t d, int k,
   __syncthreads();
   if (SLICED) {
     // a slice ends where the next one's first bucket starts (cnt[k]: the padding)
-    for (int sl = tid; sl * nb < k; sl += kBfT) ends[sl] = (uint16_t)cnt[min((sl + 1) * nb, k)];
+    if (sliced)
+      for (int sl = tid; sl * nb < k; sl += kBfT) ends[sl] = (uint16_t)cnt[min((sl + 1) * nb, k)];
     if (longrun) {
       sort4096_regs(v, key);
       store();
@@ -395,7 +410,52 @@ __global__ __launch_bounds__(kBfT) void k_bf_fold(int64_t d, int k, Cols<T> cols
 // where they average one).  4,194,304 x 65 FP64, k = 8192: 1.37 ms against 2.06
 // for bf_fold_column, whose threads own positions instead (every thread
 // looks at every position of its four, reads and writes the sums in LDS).
-constexpr int kSlAhead = 4;
+// Uneven blocks leave that loop (their second halves in flight with the rest cost the even
+// ones a tenth): they, and even ones until kSlCalm follow each other, are staged one block
+// ahead and folded with the sums in LDS.  1,000,003 x 65 FP64, k = 16,384, 64 rows in a row
+// to a bucket: 0.78 ms, 2.9 walked, 0.84 by bf_fold_column.
+constexpr int kSlAhead = 4, kSlCalm = 8;
+
+// An uneven block, staged in sg (values) and kg (sorted keys), into acc (slot m - m0 of
+// buckets m0 <= m < m1): as in bf_fold_column the thread at whose position a run starts
+// folds it, four rows at a time.
+template <typename T>
+__device__ __forceinline__ void bf_fold_uneven(const T *sg, const uint32_t *kg, uint32_t m0,
+                                               uint32_t m1, T *acc) {
+  const int p0 = 4 * threadIdx.x;
+  uint32_t kp = p0 > 0 ? kg[p0 - 1] : kBfPad;
+#pragma unroll 1
+  for (int q = 0; q < 4; ++q) {
+    const uint32_t kv = kg[p0 + q], m = bf_bucket(kv), before = bf_bucket(kp);
+    kp = kv;
+    if (m < m0 || m >= m1 || m == before) continue;
+    T s = acc[m - m0] + apply_sign(sg[kv & (kBfRows - 1)], kv);
+    int g = p0 + q + 1;
+    auto one = [&]() {   // row g, if the run goes on
+      const uint32_t kn = g < kBfRows ? kg[g] : kBfPad;
+      if (bf_bucket(kn) != m) return false;
+      s = s + apply_sign(sg[kn & (kBfRows - 1)], kn);
+      ++g;
+      return true;
+    };
+    bool on = true;
+    while (on && (g & 3)) on = one();
+    while (on && g < kBfRows) {
+      const bf_u32x4 kn = *reinterpret_cast<const bf_u32x4 *>(kg + g);
+      T xn[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) xn[e] = sg[kn[e] & (kBfRows - 1)];
+      on = bf_bucket(kn[3]) == m;   // (sorted: then all four)
+      if (!on) break;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s = s + apply_sign(xn[e], kn[e]);
+      g += 4;
+    }
+    while (one()) {
+    }
+    acc[m - m0] = s;
+  }
+}
 
 template <typename T, int B, int NS>
 __global__ __launch_bounds__(kBfT) void k_bf_fold_sliced(int64_t d, int k, Cols<T> cols, int parts,
@@ -404,8 +464,9 @@ __global__ __launch_bounds__(kBfT) void k_bf_fold_sliced(int64_t d, int k, Cols<
                                                          T *__restrict__ Y, int64_t ldy) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   // (the entries first: the one past a buffer's end is read, not used)
-  uint16_t *lent = reinterpret_cast<uint16_t *>(smem_raw);   // 2 kBfRows
+  uint16_t *lent = reinterpret_cast<uint16_t *>(smem_raw);   // 2 kBfRows, or one block's keys
   T *stage = reinterpret_cast<T *>(lent + 2 * kBfRows);      // 2 kBfRows
+  T *lacc = stage + 2 * kBfRows;                             // NS kBfT B sums
   // thread t stages 16 bytes of values kV times, kBfT threads apart (contiguous
   // across a wave, in memory and in LDS)
   constexpr int kR = 16 / (int)sizeof(T), kV = kBfRows / kBfT / kR;
@@ -436,13 +497,21 @@ __global__ __launch_bounds__(kBfT) void k_bf_fold_sliced(int64_t d, int k, Cols<
   uint16_t lo[kSlAhead][NS], hi[kSlAhead][NS];   // the slices' starts and ends, as loaded
   // the next block to fetch (past the last one: the last one again, not
   // used), uniform pointers advanced block by block
-  const T *cb = nblk > 1 ? col : col + (d - kBfRows);
-  const uint32_t *kb = keys;
-  int fb = 0;
-  auto fetch = [&](int j) {
+  const T *cb;
+  const uint32_t *kb;
+  int fb;
+  auto values_at = [&](int b) { return b < nblk - 1 ? col + (int64_t)b * kBfRows : col + (d - kBfRows); };
+  auto load_values = [&](const T *from, V (&to)[kV]) {
 #pragma unroll
     for (int q = 0; q < kV; ++q)
-      v[j][q] = *(const __attribute__((address_space(1))) Va *)(cb + kR * (tid + kBfT * q));
+      to[q] = *(const __attribute__((address_space(1))) Va *)(from + kR * (tid + kBfT * q));
+  };
+  auto put_values = [&](const V (&from)[kV], T *to) {
+#pragma unroll
+    for (int q = 0; q < kV; ++q) *reinterpret_cast<V *>(to + kR * (tid + kBfT * q)) = from[q];
+  };
+  auto fetch = [&](int j) {
+    load_values(cb, v[j]);
     ev[j] = gload(reinterpret_cast<const bf_u32x2 *>(kb) + tid);
     const uint16_t *ends = reinterpret_cast<const uint16_t *>(kb + kBfRows / 2);
 #pragma unroll
@@ -455,74 +524,139 @@ __global__ __launch_bounds__(kBfT) void k_bf_fold_sliced(int64_t d, int k, Cols<
     kb += fb < nblk ? kBfRows : 0;
   };
   auto put = [&](int j, int buf) {
-#pragma unroll
-    for (int q = 0; q < kV; ++q)
-      *reinterpret_cast<V *>(stage + buf * kBfRows + kR * (tid + kBfT * q)) = v[j][q];
+    put_values(v[j], stage + buf * kBfRows);
     *reinterpret_cast<bf_u32x2 *>(lent + buf * kBfRows + 4 * tid) = ev[j];
+  };
+  // the entries at bytes [p, pe) of eb, added to their slice's sums; sb: the values
+  auto walk = [&](const unsigned char *sb, const unsigned char *eb, uint32_t p, uint32_t pe,
+                  T (&sums)[B]) {
+    if (p >= pe) return;
+    int e = *reinterpret_cast<const int16_t *>(eb + p);
+    do {
+      // this entry's value and the next entry (at the end: one not used)
+      // are read together; the empty statement keeps the compiler from
+      // moving the second read into the next turn, behind its use
+      const uint32_t at = sizeof(T) == 8 ? (e & 0x7ff8) : ((e >> 1) & 0x3ffc);
+      T xv = *reinterpret_cast<const T *>(sb + at);
+      p += 2;
+      int en = *reinterpret_cast<const int16_t *>(eb + p);
+      asm volatile("" : "+v"(xv), "+v"(en));
+      xv = apply_sign(xv, (uint32_t)e);
+      // (adding +0.0 to the others keeps every bit: a sum from +0.0 is
+      // never -0.0; the selects before the adds, or each waits for the one before)
+      T xm[B];
+#pragma unroll
+      for (int m = 0; m < B; ++m) xm[m] = B == 1 || (e & (B - 1)) == m ? xv : T(0);
+#pragma unroll
+      for (int m = 0; m < B; ++m) sums[m] = sums[m] + xm[m];
+      e = en;
+    } while (p < pe);
   };
   uint16_t cl[NS], ch[NS];
   auto fold = [&](const T *sg, const uint16_t *le) {
-    const unsigned char *sb = reinterpret_cast<const unsigned char *>(sg);
-    const unsigned char *eb = reinterpret_cast<const unsigned char *>(le);
 #pragma unroll
-    for (int n = 0; n < NS; ++n) {
-      uint32_t p = sl[n] > 0 ? 2u * cl[n] : 0u;
-      const uint32_t pe = 2u * ch[n];
-      if (p < pe) {
-        int e = *reinterpret_cast<const int16_t *>(eb + p);
-        do {
-          // this entry's value and the next entry (at the end: one not used)
-          // are read together; the empty statement keeps the compiler from
-          // moving the second read into the next turn, behind its use
-          const uint32_t at = sizeof(T) == 8 ? (e & 0x7ff8) : ((e >> 1) & 0x3ffc);
-          T xv = *reinterpret_cast<const T *>(sb + at);
-          p += 2;
-          int en = *reinterpret_cast<const int16_t *>(eb + p);
-          asm volatile("" : "+v"(xv), "+v"(en));
-          xv = apply_sign(xv, (uint32_t)e);
-          // (adding +0.0 to the others keeps every bit: a sum from +0.0 is
-          // never -0.0)
-#pragma unroll
-          for (int m = 0; m < B; ++m)
-            acc[n][m] = acc[n][m] + (B == 1 || (e & (B - 1)) == m ? xv : T(0));
-          e = en;
-        } while (p < pe);
-      }
-    }
+    for (int n = 0; n < NS; ++n)
+      walk(reinterpret_cast<const unsigned char *>(sg), reinterpret_cast<const unsigned char *>(le),
+           sl[n] > 0 ? 2u * cl[n] : 0u, 2u * ch[n], acc[n]);
   };
+  // block at's word that tells an uneven block; in lanes 0 .. 3 those of the four from at on
+  auto tell = [&](int at) {
+    return gload(keys + (int64_t)min(at, nblk - 1) * kBfRows + kBfRows / 2);
+  };
+  const int q4 = tid & 3;
+  static_assert(kSlAhead == 4, "buffers and slots of the unrolled loop");
+  for (int b = 0; b < nblk;) {
+    uint32_t word = tell(b + q4);
+    fb = b;
+    cb = values_at(b);
+    kb = keys + (int64_t)b * kBfRows;
 #pragma unroll
-  for (int j = 0; j < kSlAhead; ++j) fetch(j);
-  put(0, 0);
-#pragma unroll
-  for (int n = 0; n < NS; ++n) {
-    cl[n] = lo[0][n];
-    ch[n] = hi[0][n];
-  }
-  fetch(0);
-  __syncthreads();
-  static_assert(kSlAhead % 2 == 0, "the staging buffer of block b0 + j is j % 2");
-  for (int b0 = 0; b0 < nblk; b0 += kSlAhead) {
-#pragma unroll
-    for (int j = 0; j < kSlAhead; ++j) {
-      if (b0 + j >= nblk) break;
-      constexpr int kNext[kSlAhead] = {1, 2, 3, 0};
-      const int jn = kNext[j], cur = j & 1;
-      uint16_t nl[NS], nh[NS];
-      put(jn, cur ^ 1);   // (after the last block: a block that is not folded)
+    for (int j = 0; j < kSlAhead; ++j) fetch(j);
+    bool odd = __any(word & kBfUneven);   // one of the next four blocks
+    if (!odd) {
+      put(0, 0);
 #pragma unroll
       for (int n = 0; n < NS; ++n) {
-        nl[n] = lo[jn][n];
-        nh[n] = hi[jn][n];
+        cl[n] = lo[0][n];
+        ch[n] = hi[0][n];
       }
-      fetch(jn);
-      fold(stage + cur * kBfRows + (b0 + j + 1 < nblk ? 0 : shift), lent + cur * kBfRows);
-#pragma unroll
-      for (int n = 0; n < NS; ++n) {
-        cl[n] = nl[n];
-        ch[n] = nh[n];
-      }
-      __syncthreads();   // this block folded, the next one staged
+      fetch(0);
+      __syncthreads();
     }
+    while (b < nblk && !odd) {
+      word = tell(b + kSlAhead + q4);
+#pragma unroll
+      for (int j = 0; j < kSlAhead; ++j) {
+        if (b >= nblk) break;
+        constexpr int kNext[kSlAhead] = {1, 2, 3, 0};
+        const int jn = kNext[j], cur = j & 1;
+        uint16_t nl[NS], nh[NS];
+        put(jn, cur ^ 1);   // (after the last block: a block that is not folded)
+#pragma unroll
+        for (int n = 0; n < NS; ++n) {
+          nl[n] = lo[jn][n];
+          nh[n] = hi[jn][n];
+        }
+        fetch(jn);
+        fold(stage + cur * kBfRows + (b + 1 < nblk ? 0 : shift), lent + cur * kBfRows);
+#pragma unroll
+        for (int n = 0; n < NS; ++n) {
+          cl[n] = nl[n];
+          ch[n] = nh[n];
+        }
+        __syncthreads();   // this block folded, the next one staged
+        ++b;
+      }
+      odd = __any(word & kBfUneven);
+    }
+    if (b >= nblk) break;
+    // four blocks with an uneven one among them: the sums in LDS (slot: bucket of this part)
+#pragma unroll
+    for (int n = 0; n < NS; ++n)
+#pragma unroll
+      for (int q = 0; q < B; ++q)
+        if (s0 + tid + kBfT * n < s1) lacc[(sl[n] - s0) * B + q] = acc[n][q];
+    V cv[kV];
+    bf_u32x4 ck;
+    uint32_t ct;
+    uint32_t *lkey = reinterpret_cast<uint32_t *>(lent);
+    auto ahead = [&](int at) {
+      ct = tell(at);
+      load_values(values_at(at), cv);
+      ck = gload(reinterpret_cast<const bf_u32x4 *>(keys + (int64_t)at * kBfRows) + tid);
+    };
+    ahead(b);
+    for (int calm = 0; b < nblk && calm < kSlCalm; ++b) {
+      put_values(cv, stage);
+      const bool unb = (__builtin_amdgcn_readfirstlane(ct) & kBfUneven) != 0;
+      if (unb && tid == kBfRows / 2 / 4 && ck[0] != kBfPad) ck[0] &= ~kBfUneven;
+      *reinterpret_cast<bf_u32x4 *>(lkey + 4 * tid) = ck;
+      __syncthreads();
+      ahead(min(b + 1, nblk - 1));
+      const T *sg = stage + (b + 1 < nblk ? 0 : shift);
+      if (unb) {
+        bf_fold_uneven(sg, lkey, (uint32_t)(s0 * B), (uint32_t)min(s1 * B, k), lacc);
+      } else {
+        const uint16_t *ends = lent + kBfRows;
+#pragma unroll 1
+        for (int s = s0 + tid; s < s1; s += kBfT) {
+          T sums[B];
+#pragma unroll
+          for (int q = 0; q < B; ++q) sums[q] = lacc[(s - s0) * B + q];
+          walk(reinterpret_cast<const unsigned char *>(sg),
+               reinterpret_cast<const unsigned char *>(lent), s > 0 ? 2u * ends[s - 1] : 0u,
+               2u * ends[s], sums);
+#pragma unroll
+          for (int q = 0; q < B; ++q) lacc[(s - s0) * B + q] = sums[q];
+        }
+      }
+      calm = unb ? 0 : calm + 1;
+      __syncthreads();
+    }
+#pragma unroll
+    for (int n = 0; n < NS; ++n)
+#pragma unroll
+      for (int q = 0; q < B; ++q) acc[n][q] = lacc[(sl[n] - s0) * B + q];
   }
 #pragma unroll
   for (int n = 0; n < NS; ++n)
@@ -700,7 +834,7 @@ hipError_t launch_bf_keys(int64_t d, int64_t k, const int32_t *h, const int8_t *
 template <typename T, int B, int NS>
 static hipError_t launch_bf_sliced(int64_t d, int64_t k, const Cols<T> &c, int parts,
                                    const uint32_t *keys, T *Y, int64_t ldy, hipStream_t st) {
-  constexpr size_t lds = (size_t)2 * kBfRows * (sizeof(T) + 2);
+  constexpr size_t lds = (size_t)2 * kBfRows * (sizeof(T) + 2) + (size_t)NS * kBfT * B * sizeof(T);
   hipError_t e = allow_dynamic_lds((const void *)k_bf_fold_sliced<T, B, NS>, (int)lds);
   if (e != hipSuccess) return e;
   const int xcds = std::max(1, dev_info().xcds);

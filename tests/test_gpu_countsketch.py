@@ -344,6 +344,35 @@ def test_sorted_slices_bit_exact(ms, orc, d, n, k, dt, hmap):
     assert bits_equal(to_host(Y), np.asfortranarray(orc.countsketch(A, h, s, k)))
 
 
+# Uneven blocks of the same fold (one slice much longer than the others of its 4096
+# rows), which keep full keys: none, one, some in a row with even ones between, fewer and more even
+# ones than it takes to go back, all, the first and the last (not whole) block, and blocks whose
+# long bucket comes first, last and at the middle key; two slices per thread, 1, 2 and 4 buckets
+# a slice, and invalid rows beside them.  Bit-exact.
+@pytest.mark.parametrize("pattern", ["u", "uu", "eu", "ue", "eeu", "ueeeu", "eeeeeu", "ueeeeeeeee",
+                                     "ueeeeeeeeeue", "euueeuuue"])
+@pytest.mark.parametrize("n,k,dt", [(2, 40, np.float64), (3, 4096, np.float32),
+                                    (2, 8192, np.float64), (65, 16384, np.float64),
+                                    (67, 9000, np.float32)])
+def test_sorted_uneven_blocks(ms, orc, pattern, n, k, dt):
+    d = 4096 * (len(pattern) - 1) + (4096 if len(pattern) % 2 else 1234)
+    d = max(d, 4096)
+    print("uneven blocks %s n=%d k=%d %s" % (pattern, n, k, dt.__name__), flush=True)
+    A = synth.normal_matrix(d, n, seed=d + k, dtype=dt)
+    h = synth.bucket_map(d, k, seed=k)
+    rng = np.random.default_rng(len(pattern))
+    for b, c in enumerate(pattern):
+        if c == "u":
+            rows = np.arange(4096 * b, min(d, 4096 * (b + 1)))
+            # from 300 rows to all of them in one bucket
+            pick = rng.random(rows.size) < (0.08, 0.5, 1.0)[b % 3]
+            h[rows[pick]] = (0, k // 2, k - 1)[(b + n) % 3]
+    s = synth.signs(d, seed=d + 1)
+    Y, ws = ms.countsketch_apply(to_dev(A), to_dev(h), to_dev(s), k, mode="sorted")
+    ms.check_status(ws)
+    assert bits_equal(to_host(Y), np.asfortranarray(orc.countsketch(A, h, s, k)))
+
+
 def test_sorted_slices_special_values(ms, orc):
     # infinities, NaN, signed zeros and the smallest subnormal keep their bits
     # (a thread adds +0.0 to the sums of its other buckets)

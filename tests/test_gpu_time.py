@@ -102,3 +102,19 @@ def test_refinement_one_row_more(ms):
 def test_refinement_nearly_empty_round(ms):
     args = (64, 1, 256, 64, torch.float64, 8)
     assert _lstsq(ms, 4300000, *args) <= 1.2 * _lstsq(ms, 4194304, *args)
+
+
+# The deterministic CountSketch with 64 rows in a row to a bucket: a block's longest chain is 64
+# adds, four times the time of even buckets at most (seven times when four buckets' chains were
+# one thread's).
+def test_sorted_uneven_buckets(ms):
+    d, n, k = 1000003, 65, 16384
+    A, Y = _normal(d, n), ms.empty_colmajor(k, n, torch.float64)
+    s = torch.randint(0, 2, (d,), generator=_gen(3), dtype=torch.int8, device="cuda") * 2 - 1
+    ws = ms.workspace(ms.workspace_size("countsketch", d=d, n=n, k=k, mode="sorted"))
+    even = torch.randint(0, k, (d,), generator=_gen(2), dtype=torch.int32, device="cuda")
+    runs = ((torch.arange(d, device="cuda") // 64) % k).int()
+    a, b = (_us(lambda: ms.countsketch_apply(A, h, s, k, Y=Y, ws=ws, mode="sorted"))
+            for h in (even, runs))
+    print("even %.1f us, runs %.1f us" % (a, b), flush=True)
+    assert b <= 4 * a
