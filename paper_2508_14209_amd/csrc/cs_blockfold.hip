@@ -800,13 +800,17 @@ int bf_sliced_parts(int ncols) {
 
 // Sliced keys are used where a fold thread then owns at most two slices (up
 // to 128 columns, and more for few buckets): 4,194,304 x 65 FP64, k = 8192:
-// 1.40 ms against 2.08 for positions; with four slices a thread (129 columns,
-// k = 8192) 3.3 against 2.4.  Fewer than 32 buckets (chains of more than 128
-// rows a block) keep the keys too.
+// 1.44 ms against 2.08 for positions; with four slices a thread (129 columns,
+// k = 8192) 3.3 against 2.4.  Two slices of two or four buckets each take longer to clear,
+// walk and store, and need a few blocks to make up for it: 5000 x 128, k = 16,384:
+// 33.8 us against 30.7, 20,000 x 100, k = 10,000: 34 and 33, 100,003 x 128: 76 and 82; k = 8192:
+// 5000 x 128 29 and 27.6, 20,000 x 128 31 and 35.  Fewer than 32 buckets (chains of more
+// than 128 rows a block) keep the keys too.
 bool cs_blockfold_sliced(int64_t d, int64_t k, int64_t ncols) {
   if (d < kBfRows || k < kBfSliceMinK || k > kBfCountMaxK || ncols < 1 || ncols > 65535) return false;
   const int64_t B = bf_slice_buckets(k), nsl = (k + B - 1) / B, parts = bf_sliced_parts((int)ncols);
-  return (nsl + parts - 1) / parts <= 2 * kBfT;
+  const int64_t own = (nsl + parts - 1) / parts;   // slices of a part
+  return own <= kBfT || (own <= 2 * kBfT && d >= (B - 1) * 4 * kBfRows);
 }
 
 hipError_t launch_bf_keys(int64_t d, int64_t k, const int32_t *h, const int8_t *s, uint32_t *keys,

@@ -373,6 +373,19 @@ def test_sorted_uneven_blocks(ms, orc, pattern, n, k, dt):
     assert bits_equal(to_host(Y), np.asfortranarray(orc.countsketch(A, h, s, k)))
 
 
+# Two slices a thread: the row counts around which they are taken (16,384 for two
+# buckets a slice, 49,152 for four), beside one slice at the same sizes.  Bit-exact.
+@pytest.mark.parametrize("d", [16383, 16384, 49151, 49152])
+@pytest.mark.parametrize("n,k", [(66, 8192), (66, 16384), (9, 16384)])
+def test_sorted_two_slices_rows(ms, orc, d, n, k):
+    print("two slices d=%d n=%d k=%d" % (d, n, k), flush=True)
+    A = synth.normal_matrix(d, n, seed=d + k)
+    h, s = synth.bucket_map(d, k, seed=d), synth.signs(d, seed=d + 1)
+    Y, ws = ms.countsketch_apply(to_dev(A), to_dev(h), to_dev(s), k, mode="sorted")
+    ms.check_status(ws)
+    assert bits_equal(to_host(Y), np.asfortranarray(orc.countsketch(A, h, s, k)))
+
+
 def test_sorted_slices_special_values(ms, orc):
     # infinities, NaN, signed zeros and the smallest subnormal keep their bits
     # (a thread adds +0.0 to the sums of its other buckets)
