@@ -631,6 +631,14 @@ __device__ __forceinline__ void cs_segment(double *acc, const Cols<T> &cols, int
   __syncthreads();
 }
 
+// Rows of a die whose codes (4 bytes each, 2.5 MB; the L2 has 4) do not stay there
+// beside the data.
+constexpr int64_t kCsSetRows = 655360;
+// Rows of a die from which six vectors in flight are better than four with several
+// bucket tiles (FP64: 4,000,000 x 33, k = 20,000, 303 -> 288 us, 2,000,000 x 8, k = 38,000,
+// 63 -> 65).
+constexpr int64_t kCsSixRows = 393216;
+
 // Persistent grid of xcds * spx workgroups.  Workgroups are dispatched to the
 // accelerator dies round-robin by id, so workgroup g runs on die g % xcds;
 // die x owns rows [x*rpx, (x+1)*rpx), so the codes of those rows are shared
@@ -638,9 +646,10 @@ __device__ __forceinline__ void cs_segment(double *acc, const Cols<T> &cols, int
 // contiguous share of the (column tile, row) space of its rows, so the bucket
 // tiles of a column are streamed by workgroups of the same die at the same
 // time, and each workgroup flushes LDS only when its share crosses a column
-// tile.  With several bucket tiles the groups first take whole column tiles, a
+// tile.  With several bucket tiles and more codes for a die's rows than its L2
+// keeps (kCsSetRows) the groups first take whole column tiles, a
 // set of them at a time, all at the same rows: one group's read of the codes
-// (as many bytes per column as FP32 data, and more than L2 holds) then serves the
+// (as many bytes per column as FP32 data) then serves the
 // others, and only the column tiles left over are shared by rows.  HBM reads went
 // from 2.3 to 1.23 times the algorithmic bytes; what bounds it now is data and code
 // of every element going from L2 to one compute unit per bucket tile, 14 TB/s in
@@ -648,13 +657,16 @@ __device__ __forceinline__ void cs_segment(double *acc, const Cols<T> &cols, int
 // vectors in flight for four; 8,388,608 x 65 FP64: 1.17 -> 1.07 ms.  A barrier per
 // step: 3.1 ms; values for the next step loaded under this one's adds: 2.54 to 2.72,
 // the more in flight the worse.  With one bucket tile the sets gain nothing and cost
-// 300,000 x 70 FP64, k = 500, 53 -> 57 us).
+// 300,000 x 70 FP64, k = 500, 53 -> 57 us; with fewer rows the codes are in L2 anyhow,
+// and the left-over columns' pieces and their flushes, all at one time, cost: 1,000,000 x 49
+// FP32, k = 32,768, 89 -> 112 us, 4,000,000 x 33 189 -> 199, 6,000,000 x 33 at k = 20,000
+// the other way round, 295 -> 277, 8,000,003 x 33 415 -> 364).
 // PART: the die's groups split its column tiles instead (whole tiles,
 // all of the die's rows), so each (column, bucket) of a die has one owner,
 // which stores its partial sum into the die's slice of a partial buffer (Y,
 // ld k, slices of k x ncols) with plain stores; k_cs_part_reduce adds the
 // slices to the output.
-template <typename T, int NT, bool VEC, int SRC, int UNR, bool NTL, bool PART>
+template <typename T, int NT, bool VEC, int SRC, int UNR, bool NTL, bool PART, bool SETS>
 __global__ __launch_bounds__(1024) void k_cs_lds_xcd(int64_t d, Cols<T> cols,
                                                      const uint32_t *__restrict__ code,
                                                      const int32_t *__restrict__ h,
@@ -689,7 +701,7 @@ __global__ __launch_bounds__(1024) void k_cs_lds_xcd(int64_t d, Cols<T> cols,
     if (bad) record_status(status, MS_ERR_RANGE);
     return;
   }
-  const int sets = nbt > 1 ? nct / subs : 0;
+  const int sets = SETS ? nct / subs : 0;
   for (int q = 0; q < sets; ++q) {
     const int c0 = (q * subs + sub) * NT;
     cs_segment<T, NT, VEC, SRC, UNR, NTL>(acc, cols, c0, min(NT, cols.ncols - c0), code, h, s, k,
@@ -926,16 +938,16 @@ hipError_t launch_batch_cs_res(int count, const ms_problem *P, const BatchEntry 
   return hipGetLastError();
 }
 
-template <typename T, int NT, bool VEC, int SRC, int UNR, bool NTL, bool PART>
+template <typename T, int NT, bool VEC, int SRC, int UNR, bool NTL, bool PART, bool SETS>
 static hipError_t launch_cs_xcd_k(int grid, size_t lds, hipStream_t st, int64_t d,
                                   const Cols<T> &c, const uint32_t *code, const int32_t *h,
                                   const int8_t *s, int64_t k, int64_t ktile, int nct, int nbt,
                                   int xcds, int spx, int64_t rpx, T *Y, int64_t ldy, int *status) {
-  const void *fn = (const void *)k_cs_lds_xcd<T, NT, VEC, SRC, UNR, NTL, PART>;
+  const void *fn = (const void *)k_cs_lds_xcd<T, NT, VEC, SRC, UNR, NTL, PART, SETS>;
   hipError_t e = allow_dynamic_lds(fn, (int)lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_cs_lds_xcd<T, NT, VEC, SRC, UNR, NTL, PART>), dim3(grid), dim3(1024),
-                     lds, st, d, c, code, h, s, k, ktile, nct, nbt, xcds, spx, rpx, Y, ldy,
+  hipLaunchKernelGGL((k_cs_lds_xcd<T, NT, VEC, SRC, UNR, NTL, PART, SETS>), dim3(grid),
+                     dim3(1024), lds, st, d, c, code, h, s, k, ktile, nct, nbt, xcds, spx, rpx, Y, ldy,
                      status);
   return hipGetLastError();
 }
@@ -951,14 +963,14 @@ static hipError_t launch_cs_xcd_v(bool vec, int grid, size_t lds, hipStream_t st
                                   int *status) {
   // vectors in flight per thread: fewer for wider column tiles (registers)
   constexpr int UNR = NT >= 8 ? 1 : NT >= 4 ? 2 : 4;
-  constexpr int UNRT = NT == 1 ? 6 : UNR;   // with several bucket tiles
+  constexpr int UNRT = NT == 1 ? 6 : UNR;   // many rows, several bucket tiles
   if constexpr (NT == 1) {
   if (part && nbt > 1) {
     hipError_t e =
-        vec ? launch_cs_xcd_k<T, NT, true, SRC, UNR, false, true>(
+        vec ? launch_cs_xcd_k<T, NT, true, SRC, UNR, false, true, false>(
                   grid, lds, st, d, c, code, h, s, k, ktile, nct, nbt, xcds, spx, rpx, part, k,
                   status)
-            : launch_cs_xcd_k<T, NT, false, SRC, UNR, false, true>(
+            : launch_cs_xcd_k<T, NT, false, SRC, UNR, false, true, false>(
                   grid, lds, st, d, c, code, h, s, k, ktile, nct, nbt, xcds, spx, rpx, part, k,
                   status);
     if (e != hipSuccess) return e;
@@ -970,17 +982,21 @@ static hipError_t launch_cs_xcd_v(bool vec, int grid, size_t lds, hipStream_t st
     return hipGetLastError();
   }
   }
-  if (nbt > 1)  // bucket tiles re-read A: ordinary loads, so the die's L2 keeps it
-    return vec ? launch_cs_xcd_k<T, NT, true, SRC, UNRT, false, false>(
-                     grid, lds, st, d, c, code, h, s, k, ktile, nct, nbt, xcds, spx, rpx, Y, ldy,
-                     status)
-               : launch_cs_xcd_k<T, NT, false, SRC, UNRT, false, false>(
-                     grid, lds, st, d, c, code, h, s, k, ktile, nct, nbt, xcds, spx, rpx, Y, ldy,
-                     status);
-  return vec ? launch_cs_xcd_k<T, NT, true, SRC, UNR, true, false>(
+  // bucket tiles re-read A: ordinary loads, so the die's L2 keeps it
+#define MS_TILES(VEC_, UNR_, SETS_)                                                               \
+  launch_cs_xcd_k<T, NT, VEC_, SRC, UNR_, false, false, SETS_>(grid, lds, st, d, c, code, h, s, k, \
+                                                               ktile, nct, nbt, xcds, spx, rpx, Y, \
+                                                               ldy, status)
+  if (nbt > 1 && rpx >= kCsSetRows)
+    return vec ? MS_TILES(true, UNRT, true) : MS_TILES(false, UNRT, true);
+  if (nbt > 1 && rpx >= kCsSixRows)
+    return vec ? MS_TILES(true, UNRT, false) : MS_TILES(false, UNRT, false);
+  if (nbt > 1) return vec ? MS_TILES(true, UNR, false) : MS_TILES(false, UNR, false);
+#undef MS_TILES
+  return vec ? launch_cs_xcd_k<T, NT, true, SRC, UNR, true, false, false>(
                    grid, lds, st, d, c, code, h, s, k, ktile, nct, nbt, xcds, spx, rpx, Y, ldy,
                    status)
-             : launch_cs_xcd_k<T, NT, false, SRC, UNR, true, false>(
+             : launch_cs_xcd_k<T, NT, false, SRC, UNR, true, false, false>(
                    grid, lds, st, d, c, code, h, s, k, ktile, nct, nbt, xcds, spx, rpx, Y, ldy,
                    status);
 }

@@ -175,6 +175,35 @@ def test_countsketch_column_sets(ms, orc, d, n, k, dtype):
     assert rel(to_host(Y), orc.countsketch(A, h, s, k)) <= (1e-12 if dtype == np.float64 else 1e-5)
 
 
+# The same sets where they are taken (655,360 rows to a die), one row before, and with left-over
+# columns, against FP64 sums by torch.
+@pytest.mark.parametrize("d,n,k,dtype", [(8 * 655360, 17, 32768, np.float32),
+                                         (8 * 655360 - 8, 17, 32768, np.float32),
+                                         (8 * 655360 + 13, 33, 20000, np.float32),
+                                         (8 * 655360 + 8, 12, 40000, np.float64)])
+def test_countsketch_column_sets_many_rows(ms, d, n, k, dtype):
+    import torch
+    print("column sets d=%d n=%d k=%d %s" % (d, n, k, np.dtype(dtype)), flush=True)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    dt = torch.float64 if dtype == np.float64 else torch.float32
+    A = torch.randn((n, d), generator=g, device="cuda", dtype=dt).t()
+    h = torch.randint(0, k, (d,), generator=g, device="cuda", dtype=torch.int32)
+    s = torch.randint(0, 2, (d,), generator=g, device="cuda", dtype=torch.int8) * 2 - 1
+    code, _ = ms.pack_sketch(h, s, k)
+    Y = ms.empty_colmajor(k, n, dt, "cuda")
+    Y.zero_()
+    ws = ms.workspace(256, "cuda")
+    ms.countsketch_accumulate(A, code, k, Y, mode="lds", ws=ws)
+    ms.check_status(ws)
+    ref = torch.zeros((k, n), device="cuda", dtype=torch.float64)
+    for j in range(0, n, 8):
+        ref[:, j:j + 8] = torch.zeros((k, min(8, n - j)), device="cuda",
+                                      dtype=torch.float64).index_add_(
+            0, h.long(), A[:, j:j + 8].double() * s.double()[:, None])
+    err = (Y.double() - ref).norm().item() / ref.norm().item()
+    assert err <= (1e-12 if dtype == np.float64 else 1e-5)
+
+
 @pytest.mark.parametrize("d,n,k,dtype,one", [
     (7679, 3, 65536, np.float32, None), (7680, 2, 131072, np.float64, None),
     (7681, 5, 131072, np.float32, None), (7680 * 21 + 1, 37, 163841, np.float32, None),

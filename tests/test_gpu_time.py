@@ -118,3 +118,20 @@ def test_sorted_uneven_buckets(ms):
             for h in (even, runs))
     print("even %.1f us, runs %.1f us" % (a, b), flush=True)
     assert b <= 4 * a
+
+
+# Two bucket tiles over data that the caches hold: one column more than three for each of a die's
+# groups costs no more than an even share (a quarter more when the left-over column's pieces were
+# flushed all at one time).
+def test_two_tiles_left_over_column(ms):
+    def us(n):
+        d, k = 1000000, 32768
+        A, Y = _normal(d, n, torch.float32), ms.empty_colmajor(k, n, torch.float32)
+        h = torch.randint(0, k, (d,), generator=_gen(2), dtype=torch.int32, device="cuda")
+        s = torch.randint(0, 2, (d,), generator=_gen(3), dtype=torch.int8, device="cuda") * 2 - 1
+        ws = ms.workspace(ms.workspace_size("countsketch", d=d, n=n, k=k, a_dtype=ms.MS_F32))
+        t = _us(lambda: ms.countsketch_apply(A, h, s, k, Y=Y, ws=ws), 24)
+        print("n=%d: %.1f us" % (n, t), flush=True)
+        return t
+
+    assert us(49) <= 1.12 * us(48)
