@@ -11,7 +11,12 @@
  *  - All array arguments are DEVICE pointers owned by the caller.  The library
  *    allocates no memory on any call; scratch space comes from the caller's
  *    workspace `ws` of `ws_bytes` bytes, sized by ms_workspace_size() and
- *    aligned to 256 bytes.
+ *    aligned to 256 bytes.  Products in FP64 and the Gram pass of wide normal
+ *    equations and rand_cholQR (n + nrhs > 80 or n > 64; up to 80 MB of
+ *    partial sums) also run, over fewer workgroups, in a smaller workspace
+ *    down to what their partial sums needed before they took the whole chip
+ *    (17 MB).  Their results then differ in the order of the sums.  Anything
+ *    smaller is MS_ERR_NOMEM.
  *  - Matrices are column-major with a leading dimension (LAPACK style):
  *    element (i, j) of M is M[i + j*ldm], ldm >= number of rows.
  *  - The CountSketch S (k x d) of Def. 3 is given by a bucket map h (int32,
@@ -49,7 +54,7 @@ typedef enum {
   MS_OK = 0,
   MS_ERR_ARG = 1,         /* invalid argument, detected on the host */
   MS_ERR_RANGE = 2,       /* h outside [0,k) or s not in {+1,-1} (device) */
-  MS_ERR_NOMEM = 3,       /* workspace smaller than ms_workspace_size() */
+  MS_ERR_NOMEM = 3,       /* workspace too small */
   MS_ERR_SINGULAR = 4,    /* R has a zero or non-finite diagonal (device) */
   MS_ERR_DEVICE = 5,      /* a HIP runtime call or kernel launch failed */
   MS_ERR_UNSUPPORTED = 6  /* valid but unsupported combination or size */

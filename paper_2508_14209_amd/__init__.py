@@ -194,7 +194,10 @@ def workspace(nbytes: int, device="cuda") -> torch.Tensor:
     return torch.empty(int(nbytes) + 256, dtype=torch.uint8, device=device)
 
 
-def _ws_ptr(ws: torch.Tensor, need: int):
+def _ws_ptr(ws: torch.Tensor, need: int = 256):
+    # (256: only the status word; the call itself says whether the rest is
+    # enough, for the operations that also run in a smaller workspace than
+    # workspace_size() gives)
     p = ws.data_ptr()
     aligned = (p + 255) // 256 * 256
     have = ws.numel() - (aligned - p)
@@ -417,7 +420,7 @@ def gaussian_apply(G: torch.Tensor, Y: torch.Tensor, Z: torch.Tensor | None = No
     Zp, ldz = colmajor(Z, "Z")
     need = workspace_size("gaussian", n=nc, k=k, k2=k2, a_dtype=y_dt, g_dtype=g_dt)
     ws = workspace(need, Y.device) if ws is None else ws
-    wp, have = _ws_ptr(ws, need)
+    wp, have = _ws_ptr(ws)
     _ok(_lib.ms_gaussian_apply(k, nc, k2, g_dt, Gp, ldg, y_dt, Yp, ldy, Zp, ldz, wp, have,
                                _stream(stream)), "ms_gaussian_apply")
     return Z, ws
@@ -441,7 +444,7 @@ def multisketch_apply(A: torch.Tensor, h: torch.Tensor, s: torch.Tensor, G: torc
     need = workspace_size("multisketch", d=d, n=n, k=k, k2=k2, a_dtype=a_dt, g_dtype=g_dt,
                           mode=mode)
     ws = workspace(need, A.device) if ws is None else ws
-    wp, have = _ws_ptr(ws, need)
+    wp, have = _ws_ptr(ws)
     o = _opts(mode, y_terms=y_terms)
     _ok(_lib.multisketch_apply(d, n, k, k2, a_dt, Ap, lda,
                                _vec(h, torch.int32, "h") if d else None,
@@ -494,7 +497,7 @@ def sketch_lstsq(A: torch.Tensor, B: torch.Tensor, h: torch.Tensor, s: torch.Ten
     need = workspace_size("lstsq", d=d, n=n, nrhs=nrhs, k=k, k2=k2, a_dtype=a_dt,
                           g_dtype=g_dt, mode=mode, refine_steps=refine_steps)
     ws = workspace(need, A.device) if ws is None else ws
-    wp, have = _ws_ptr(ws, need)
+    wp, have = _ws_ptr(ws)
     o = _opts(mode, refine_steps, tile_cols, schedule, y_terms=y_terms)
     _ok(_lib.sketch_lstsq(d, n, nrhs, k, k2, a_dt, Ap, lda, Bp, ldb, _vec(h, torch.int32, "h"),
                           _vec(s, torch.int8, "s"), g_dt, Gp, ldg, Xp, ldx, ctypes.byref(o), wp,
@@ -562,7 +565,7 @@ def rand_cholqr_lstsq(A: torch.Tensor, B: torch.Tensor, h: torch.Tensor, s: torc
     need = workspace_size("rand_cholqr", d=d, n=n, nrhs=nrhs, k=k, k2=k2, a_dtype=a_dt,
                           g_dtype=g_dt, mode=mode)
     ws = workspace(need, A.device) if ws is None else ws
-    wp, have = _ws_ptr(ws, need)
+    wp, have = _ws_ptr(ws)
     o = _opts(mode, 0, y_terms=y_terms)
     _ok(_lib.rand_cholqr_lstsq(d, n, nrhs, k, k2, a_dt, Ap, lda, Bp, ldb, _vec(h, torch.int32, "h"),
                                _vec(s, torch.int8, "s"), g_dt, Gp, ldg, Xp, ldx, Rp, ldr,
@@ -592,7 +595,7 @@ def normal_equations_lstsq(A: torch.Tensor, B: torch.Tensor, X: torch.Tensor | N
     Rp, ldr = colmajor(R, "R") if R is not None else (None, n)
     need = workspace_size("normal_equations", d=d, n=n, nrhs=nrhs, a_dtype=a_dt)
     ws = workspace(need, A.device) if ws is None else ws
-    wp, have = _ws_ptr(ws, need)
+    wp, have = _ws_ptr(ws)
     _ok(_lib.normal_equations_lstsq(d, n, nrhs, a_dt, Ap, lda, Bp, ldb, Xp, ldx, Rp, ldr, None,
                                     wp, have, _stream(stream)), "normal_equations_lstsq")
     return X, R, ws

@@ -125,17 +125,25 @@ struct LstsqLayout {
   CsLayout cs;
   size_t y = 0, partials = 0, z64 = 0, qr = 0, fact = 0, tau = 0;
   size_t r = 0, yr = 0, zr = 0, gv = 0, dx = 0;
+  GemmPlan gemm{};
   size_t total = 0;
 };
 
+// Layouts with a lean flag.  ms_workspace_size() gives the size of the full
+// one, whose partials take the whole chip.  A workspace that is smaller is
+// laid out lean (fewer K splits of an FP64 product, fewer workgroups of the
+// wide Gram pass), so that a buffer kept from a time when the query gave less
+// still serves; only one too small for that is MS_ERR_NOMEM.
 LstsqLayout lstsq_layout(int64_t d, int64_t n, int64_t nrhs, int64_t k, int64_t k2,
-                         ms_dtype a_dtype, ms_dtype g_dtype, int mode, int refine) {
+                         ms_dtype a_dtype, ms_dtype g_dtype, int mode, int refine,
+                         bool lean = false) {
   LstsqLayout L;
   Carve cv;
   const int64_t nc = n + nrhs;
   carve_cs(cv, L.cs, d, k, mode, nc, dtype_size(a_dtype));
   L.y = cv.take((size_t)k * nc * dtype_size(a_dtype));
-  L.partials = cv.take(plan_gemm(k2, nc, k, g_dtype).partial_bytes);
+  L.gemm = plan_gemm(k2, nc, k, g_dtype, lean);
+  L.partials = cv.take(L.gemm.partial_bytes);
   L.z64 = cv.take((size_t)k2 * nc * 8);
   L.qr = cv.take(qr_workspace_bytes(k2, n, nrhs));
   L.fact = cv.take((size_t)k2 * n * 8);
@@ -160,7 +168,9 @@ struct RcqLayout {
   CsLayout cs;
   size_t y = 0, partials = 0, z64 = 0, qr = 0, fact = 0, tau = 0;
   size_t r0 = 0, rinv = 0, part = 0, w = 0, q0 = 0, bad = 0, total = 0;
+  GemmPlan gemm{};
   bool wide = false;
+  int chunks = 0;  // workgroups of the wide Gram pass
 };
 
 bool rcq_is_wide(int64_t n, int64_t nrhs) {
@@ -171,12 +181,13 @@ bool rcq_fits_wide(int64_t n, int64_t nrhs) {
 }
 
 RcqLayout rcq_layout(int64_t d, int64_t n, int64_t nrhs, int64_t k, int64_t k2,
-                     ms_dtype a_dtype, ms_dtype g_dtype, int mode) {
+                     ms_dtype a_dtype, ms_dtype g_dtype, int mode, bool lean = false) {
   RcqLayout L;
   Carve cv;
   carve_cs(cv, L.cs, d, k, mode, n, dtype_size(a_dtype));
   L.y = cv.take((size_t)k * n * dtype_size(a_dtype));
-  L.partials = cv.take(plan_gemm(k2, n, k, g_dtype).partial_bytes);
+  L.gemm = plan_gemm(k2, n, k, g_dtype, lean);
+  L.partials = cv.take(L.gemm.partial_bytes);
   L.z64 = cv.take((size_t)k2 * n * 8);
   L.qr = cv.take(qr_workspace_bytes(k2, n, 0));
   L.fact = cv.take((size_t)k2 * n * 8);
@@ -186,7 +197,8 @@ RcqLayout rcq_layout(int64_t d, int64_t n, int64_t nrhs, int64_t k, int64_t k2,
     const int nc = (int)(n + nrhs);
     L.rinv = cv.take((size_t)n * n * 8);
     L.q0 = cv.take((size_t)d * n * 8);
-    L.part = cv.take(gram_wide_partial_bytes(d, nc));
+    L.chunks = gram_wide_chunks(d, nc, lean);
+    L.part = cv.take(gram_wide_partial_bytes(d, nc, lean));
     L.w = cv.take(gram_wide_w_bytes(nc));
     L.bad = cv.take(4);
   } else {
@@ -227,16 +239,18 @@ CsrLayout csr_layout(int64_t d, int64_t n, int64_t nrhs, int64_t k1, int64_t k2,
 // Gram matrix and the factorisation's breakdown flag.
 struct NeLayout {
   size_t part = 0, w = 0, bad = 0, total = 0;
+  int chunks = 0;  // workgroups of the wide Gram pass
 };
 
 bool ne_is_wide(int64_t n, int64_t nrhs) { return rcq_is_wide(n, nrhs); }
 bool ne_fits_wide(int64_t n, int64_t nrhs) { return rcq_fits_wide(n, nrhs); }
 
-NeLayout ne_layout(int64_t d, int64_t n, int64_t nrhs) {
+NeLayout ne_layout(int64_t d, int64_t n, int64_t nrhs, bool lean = false) {
   NeLayout L;
   Carve cv;
   if (ne_is_wide(n, nrhs) && ne_fits_wide(n, nrhs)) {
-    L.part = cv.take(gram_wide_partial_bytes(d, (int)(n + nrhs)));
+    L.chunks = gram_wide_chunks(d, (int)(n + nrhs), lean);
+    L.part = cv.take(gram_wide_partial_bytes(d, (int)(n + nrhs), lean));
     L.w = cv.take(gram_wide_w_bytes((int)(n + nrhs)));
     L.bad = cv.take(4);
   } else {
@@ -554,14 +568,16 @@ ms_status ms_gaussian_apply(int64_t k, int64_t ncols, int64_t k2, ms_dtype g_dty
   if (!ok) return MS_ERR_ARG;
   if (ldg < k2 || ldy < k || ldz < k2) return MS_ERR_ARG;
   if (!ws || (ncols > 0 && (!G || !Y || !Z))) return MS_ERR_ARG;
-  if (ws_bytes < ms_workspace_size(MS_OP_GAUSSIAN, 0, ncols, 0, k, k2, y_dtype, g_dtype, nullptr))
-    return MS_ERR_NOMEM;
+  Carve cv;
+  const size_t o_part = cv.off;
+  GemmPlan p = plan_gemm(k2, ncols, k, g_dtype);
+  if (ws_bytes < o_part + align_up(std::max<size_t>(1, p.partial_bytes)))
+    p = plan_gemm(k2, ncols, k, g_dtype, true);
+  cv.take(p.partial_bytes);
+  if (ws_bytes < cv.off) return MS_ERR_NOMEM;
   hipStream_t st = (hipStream_t)stream;
   hipError_t e = launch_zero_status(static_cast<int *>(ws), st);
   if (e != hipSuccess || ncols == 0) return from_hip(e);
-  Carve cv;
-  const GemmPlan p = plan_gemm(k2, ncols, k, g_dtype);
-  const size_t o_part = cv.take(p.partial_bytes);
   e = launch_gemm(p, g_dtype, G, ldg, Y, ldy, Z, ldz, nullptr, at<void>(ws, o_part), nullptr, st);
   return from_hip(e);
 }
@@ -580,18 +596,20 @@ ms_status multisketch_apply(int64_t d, int64_t n, int64_t k, int64_t k2, ms_dtyp
   if (mode == MS_CS_SORTED && d > kMax31) return MS_ERR_UNSUPPORTED;
   if (lda < (d > 1 ? d : 1) || ldg < k2 || ldz < k2) return MS_ERR_ARG;
   if (!ws || (n > 0 && (!Z || !G)) || (d > 0 && n > 0 && (!A || !h || !s))) return MS_ERR_ARG;
-  if (ws_bytes < ms_workspace_size(MS_OP_MULTISKETCH, d, n, 0, k, k2, a_dtype, g_dtype, opts))
-    return MS_ERR_NOMEM;
-  hipStream_t st = (hipStream_t)stream;
-  int *status = static_cast<int *>(ws);
-  if (n == 0) return from_hip(launch_zero_status(status, st));
-  hipError_t e;
   Carve cv;
   CsLayout L;
   carve_cs(cv, L, d, k, mode, n, dtype_size(a_dtype));
   const size_t o_y = cv.take((size_t)k * n * dtype_size(a_dtype));
-  const GemmPlan p = plan_gemm(k2, n, k, g_dtype);
-  const size_t o_part = cv.take(p.partial_bytes);
+  const size_t o_part = cv.off;
+  GemmPlan p = plan_gemm(k2, n, k, g_dtype);
+  if (ws_bytes < o_part + align_up(std::max<size_t>(1, p.partial_bytes)))
+    p = plan_gemm(k2, n, k, g_dtype, true);
+  cv.take(p.partial_bytes);
+  if (ws_bytes < cv.off) return MS_ERR_NOMEM;
+  hipStream_t st = (hipStream_t)stream;
+  int *status = static_cast<int *>(ws);
+  if (n == 0) return from_hip(launch_zero_status(status, st));
+  hipError_t e;
   if (a_dtype == MS_F64) {
     Cols<double> c{static_cast<const double *>(A), lda, nullptr, 0, (int)n, (int)n};
     e = run_countsketch<double>(d, k, c, h, s, at<double>(ws, o_y), k, mode, ws, L, status, st, tuning_of(opts));
@@ -644,7 +662,9 @@ ms_status sketch_lstsq(int64_t d, int64_t n, int64_t nrhs, int64_t k, int64_t k2
   if (mode == MS_CS_SORTED && d > kMax31) return MS_ERR_UNSUPPORTED;
   if (lda < d || ldb < d || ldg < k2 || ldx < n) return MS_ERR_ARG;
   if (!A || !B || !h || !s || !G || !X || !ws) return MS_ERR_ARG;
-  const LstsqLayout L = lstsq_layout(d, n, nrhs, k, k2, a_dtype, g_dtype, mode, refine);
+  LstsqLayout L = lstsq_layout(d, n, nrhs, k, k2, a_dtype, g_dtype, mode, refine);
+  if (ws_bytes < L.total)
+    L = lstsq_layout(d, n, nrhs, k, k2, a_dtype, g_dtype, mode, refine, true);
   if (ws_bytes < L.total) return MS_ERR_NOMEM;
   hipStream_t st = (hipStream_t)stream;
   int *status = static_cast<int *>(ws);
@@ -662,10 +682,9 @@ ms_status sketch_lstsq(int64_t d, int64_t n, int64_t nrhs, int64_t k, int64_t k2
   }
   // 2. Z = G Y (split-K partials reduced in split order into an FP64 Z);
   // 3. Householder QR of Z_A, Q^T Z_B, back substitution
-  const GemmPlan p = plan_gemm(k2, nc, k, g_dtype);
   double *z64 = at<double>(ws, L.z64);
   if (e == hipSuccess)
-    e = launch_gemm(p, g_dtype, G, ldg, at<void>(ws, L.y), k, nullptr, k2, z64,
+    e = launch_gemm(L.gemm, g_dtype, G, ldg, at<void>(ws, L.y), k, nullptr, k2, z64,
                     at<void>(ws, L.partials), nullptr, st, yterms_of(opts));
   if (e == hipSuccess)
     e = launch_qr_solve(k2, n, nrhs, z64, k2, z64 + n * k2, k2, X, ldx, nullptr, 0,
@@ -729,7 +748,8 @@ ms_status rand_cholqr_lstsq(int64_t d, int64_t n, int64_t nrhs, int64_t k, int64
   if (mode == MS_CS_SORTED && d > kMax31) return MS_ERR_UNSUPPORTED;
   if (lda < d || ldb < d || ldg < k2 || ldx < n || (R && ldr < n)) return MS_ERR_ARG;
   if (!A || !B || !h || !s || !G || !X || !ws) return MS_ERR_ARG;
-  const RcqLayout L = rcq_layout(d, n, nrhs, k, k2, a_dtype, g_dtype, mode);
+  RcqLayout L = rcq_layout(d, n, nrhs, k, k2, a_dtype, g_dtype, mode);
+  if (ws_bytes < L.total) L = rcq_layout(d, n, nrhs, k, k2, a_dtype, g_dtype, mode, true);
   if (ws_bytes < L.total) return MS_ERR_NOMEM;
   hipStream_t st = (hipStream_t)stream;
   int *status = static_cast<int *>(ws);
@@ -744,10 +764,9 @@ ms_status rand_cholqr_lstsq(int64_t d, int64_t n, int64_t nrhs, int64_t k, int64
     e = run_countsketch<float>(d, k, c, h, s, at<float>(ws, L.y), k, mode, ws, L.cs, status, st,
                                tuning_of(opts));
   }
-  const GemmPlan p = plan_gemm(k2, n, k, g_dtype);
   double *z64 = at<double>(ws, L.z64);
   if (e == hipSuccess)
-    e = launch_gemm(p, g_dtype, G, ldg, at<void>(ws, L.y), k, nullptr, k2, z64,
+    e = launch_gemm(L.gemm, g_dtype, G, ldg, at<void>(ws, L.y), k, nullptr, k2, z64,
                     at<void>(ws, L.partials), nullptr, st, yterms_of(opts));
   double *fact = at<double>(ws, L.fact), *rinv = at<double>(ws, L.rinv);
   if (L.wide) {
@@ -765,9 +784,11 @@ ms_status rand_cholqr_lstsq(int64_t d, int64_t n, int64_t nrhs, int64_t k, int64
     if (e == hipSuccess)
       e = a_dtype == MS_F64
               ? launch_gram_wide<double, double>(d, (int)n, nc, q0, d,
-                                                 static_cast<const double *>(B), ldb, part, W, st)
+                                                 static_cast<const double *>(B), ldb, L.chunks,
+                                                 part, W, st)
               : launch_gram_wide<double, float>(d, (int)n, nc, q0, d,
-                                                static_cast<const float *>(B), ldb, part, W, st);
+                                                static_cast<const float *>(B), ldb, L.chunks, part,
+                                                W, st);
     // 5-8. R1 = chol(Q0^T Q0), y = R1^{-T} Q0^T B, x = R0^{-1} R1^{-1} y, R = R1 R0
     if (e == hipSuccess)
       e = launch_chol_solve_wide((int)n, (int)nrhs, nc, W, fact, k2, X, ldx, R, ldr,
@@ -923,7 +944,8 @@ ms_status normal_equations_lstsq(int64_t d, int64_t n, int64_t nrhs, ms_dtype a_
   if (wide && !ne_fits_wide(n, nrhs)) return MS_ERR_UNSUPPORTED;
   if (lda < d || ldb < d || ldx < n || (R && ldr < n)) return MS_ERR_ARG;
   if (!A || !B || !X || !ws) return MS_ERR_ARG;
-  const NeLayout L = ne_layout(d, n, nrhs);
+  NeLayout L = ne_layout(d, n, nrhs);
+  if (ws_bytes < L.total) L = ne_layout(d, n, nrhs, true);
   if (ws_bytes < L.total) return MS_ERR_NOMEM;
   hipStream_t st = (hipStream_t)stream;
   int *status = static_cast<int *>(ws);
@@ -938,9 +960,11 @@ ms_status normal_equations_lstsq(int64_t d, int64_t n, int64_t nrhs, ms_dtype a_
     if (e == hipSuccess)
       e = a_dtype == MS_F64
               ? launch_gram_wide<double, double>(d, (int)n, nc, static_cast<const double *>(A), lda,
-                                                 static_cast<const double *>(B), ldb, part, W, st)
+                                                 static_cast<const double *>(B), ldb, L.chunks,
+                                                 part, W, st)
               : launch_gram_wide<float, float>(d, (int)n, nc, static_cast<const float *>(A), lda,
-                                               static_cast<const float *>(B), ldb, part, W, st);
+                                               static_cast<const float *>(B), ldb, L.chunks, part,
+                                               W, st);
     if (e == hipSuccess)
       e = launch_chol_solve_wide((int)n, (int)nrhs, nc, W, nullptr, 0, X, ldx, R, ldr,
                                  at<int>(ws, L.bad), status, st);

@@ -966,7 +966,7 @@ hipError_t launch_batch_reduce(int count, ms_dtype g_dtype, const ms_problem *P,
   return hipGetLastError();
 }
 
-GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, ms_dtype g_dtype) {
+GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, ms_dtype g_dtype, bool lean) {
   GemmPlan p{};
   p.M = (int)M;
   p.N = (int)N;
@@ -984,15 +984,16 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, ms_dtype g_dtype) {
   int64_t ns;
   if (f64) {
     // FP64: 128 x (16 NB) tiles, at most one workgroup per compute unit, at
-    // least 128 K values each.  Where the sketch alone fits
-    // sketch_lstsq_noalloc's scratch array, no more partials than
-    // ceil(1024 / (64 x 64 tiles)) splits make: its limit is stated with them.
+    // least 128 K values each.  A lean plan, and every plan whose sketch
+    // alone fits sketch_lstsq_noalloc's scratch array, has no more partials
+    // than ceil(1024 / (64 x 64 tiles)) splits make: that array's limit is
+    // stated with them, and callers keep workspaces that were sized for them.
     // If the splits leave compute units idle, the column blocks go to more,
     // narrower tiles (128 x 8192 . 8192 x 65, 64 splits: one 80-column tile
     // 20.6 us on 64 compute units, three 32-column tiles 12.8 us).
     const int64_t t64 = std::max<int64_t>(1, ((M + 63) / 64) * ((N + 63) / 64));
     int64_t cap = kmax;
-    if (K * N * 8 <= MS_NOALLOC_SCRATCH_BYTES) cap = std::min(cap, (1024 + t64 - 1) / t64);
+    if (lean || K * N * 8 <= MS_NOALLOC_SCRATCH_BYTES) cap = std::min(cap, (1024 + t64 - 1) / t64);
     const int64_t nblk = std::max<int64_t>(1, (N + 15) / 16), tm = std::max(1, p.tiles_m);
     const int64_t tn = std::max((nblk + kDMaxNB - 1) / kDMaxNB,
                                 std::min(nblk, target / (tm * std::max<int64_t>(1, cap))));

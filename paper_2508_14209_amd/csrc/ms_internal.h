@@ -152,7 +152,8 @@ struct GemmPlan {
   size_t partial_bytes;  // workspace for the split-K partials
   size_t ybf16_bytes;    // workspace for the BF16 copy of Y (BF16 path)
 };
-GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, ms_dtype g_dtype);
+// lean: partials no larger than in workspaces that callers may have kept.
+GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, ms_dtype g_dtype, bool lean = false);
 // z64 (optional) receives an FP64 copy of Z (ldz64 = M).
 // yterms: for a BF16 G, Y enters as 1 BF16 term (rounded) or as 3 BF16
 // terms whose sum is Y exactly.
@@ -620,12 +621,14 @@ hipError_t launch_cs_tiled(int64_t d, int64_t k, const Cols<T> &c, const void *p
 constexpr int kWideMaxN = 256;
 constexpr int kWideMaxRhs = 16;
 constexpr int kWideMaxCols = 272;
-int gram_wide_chunks(int64_t d, int nc);
-size_t gram_wide_partial_bytes(int64_t d, int nc);
+// Workgroups of the Gram pass and the bytes of their partials.  lean: as
+// many as fit the partials of workspaces that callers may have kept.
+int gram_wide_chunks(int64_t d, int nc, bool lean);
+size_t gram_wide_partial_bytes(int64_t d, int nc, bool lean);
 size_t gram_wide_w_bytes(int nc);
 template <typename TX, typename TB>
 hipError_t launch_gram_wide(int64_t d, int nx, int nc, const TX *X, int64_t ldx, const TB *B,
-                            int64_t ldb, double *part, double *W, hipStream_t st);
+                            int64_t ldb, int nchunks, double *part, double *W, hipStream_t st);
 // rand_cholQR for wide problems (rcq_wide.hip): Rinv (n x n, ld n) = R0^{-1}
 // from the upper part of the QR factors (ld ldf), then Q0 = A Rinv (d x n
 // FP64, ld d).  A zero or non-finite diagonal of R0 records MS_ERR_SINGULAR.

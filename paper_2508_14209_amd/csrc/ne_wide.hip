@@ -607,15 +607,34 @@ int wide_nt(int nc) { return (nc + 15) / 16; }
 // Workgroups of the wide Gram pass: one per compute unit, each with at least
 // four slabs, so that writing and adding a workgroup's tiles (2 KB each) stays
 // below the time of its products.
-int gram_wide_chunks(int64_t d, int nc) {
-  const GramShape g = gram_shape(wide_nt(nc));
+//
+// Those partials are up to 80 MB (256 columns).  Lean: as many workgroups as
+// find room in the partials of a task per wave, which workspaces that callers
+// keep may have been sized for: np x np doubles for each of the chunks that
+// give 2 x CUs tasks of 2 x 4 tiles, rounded up to the dies, at least 64 slabs
+// of 16 rows in each (9 to 17 MB).  np x np doubles hold at least one
+// workgroup's tiles, so there is always room.
+int gram_wide_chunks(int64_t d, int nc, bool lean) {
+  const int NT = wide_nt(nc);
+  const GramShape g = gram_shape(NT);
   const int64_t nslab = (d + 16 * g.groups - 1) / (16 * g.groups);
-  return (int)std::max<int64_t>(1, std::min<int64_t>(dev_info().cus, nslab / 4));
+  int64_t c = std::min<int64_t>(dev_info().cus, nslab / 4);
+  if (lean) {
+    const DevInfo &di = dev_info();
+    const int xcds = std::max(1, di.xcds);
+    int ntasks = 0;
+    for (int a = 0; a < NT; a += 2) ntasks += (NT - a + 3) / 4;
+    int64_t m = std::max<int64_t>(1, 2 * di.cus / ntasks);
+    m = std::min<int64_t>(m, std::max<int64_t>(1, (d + 15) / 16 / 64));
+    m = std::min<int64_t>((m + xcds - 1) / xcds * xcds, 4096);
+    c = std::min<int64_t>(c, m * NT * NT / (g.groups * g.ntiles));
+  }
+  return (int)std::max<int64_t>(1, c);
 }
 
-size_t gram_wide_partial_bytes(int64_t d, int nc) {
+size_t gram_wide_partial_bytes(int64_t d, int nc, bool lean) {
   const GramShape g = gram_shape(wide_nt(nc));
-  return (size_t)gram_wide_chunks(d, nc) * g.groups * g.ntiles * 256 * sizeof(double);
+  return (size_t)gram_wide_chunks(d, nc, lean) * g.groups * g.ntiles * 256 * sizeof(double);
 }
 
 size_t gram_wide_w_bytes(int nc) {
@@ -640,11 +659,10 @@ static hipError_t launch_gram_nt(int64_t d, const TX *X, int64_t ldx, const TB *
 
 template <typename TX, typename TB>
 hipError_t launch_gram_wide(int64_t d, int nx, int nc, const TX *X, int64_t ldx, const TB *B,
-                            int64_t ldb, double *part, double *W, hipStream_t st) {
+                            int64_t ldb, int nchunks, double *part, double *W, hipStream_t st) {
   if (nc < 1 || nc > kWideMaxCols || nx < 0 || nx > nc) return hipErrorInvalidValue;
   const int NT = wide_nt(nc), np = 16 * NT;
   const GramShape g = gram_shape(NT);
-  const int nchunks = gram_wide_chunks(d, nc);
   hipError_t e = hipErrorInvalidValue;
   // (up to 64 columns the fused pass of randcholqr.hip is taken: n > 64 or
   // n + nrhs > 80 here, at least five tile columns)
@@ -662,14 +680,14 @@ hipError_t launch_gram_wide(int64_t d, int nx, int nc, const TX *X, int64_t ldx,
   return hipGetLastError();
 }
 template hipError_t launch_gram_wide<double, double>(int64_t, int, int, const double *, int64_t,
-                                                     const double *, int64_t, double *, double *,
-                                                     hipStream_t);
+                                                     const double *, int64_t, int, double *,
+                                                     double *, hipStream_t);
 template hipError_t launch_gram_wide<float, float>(int64_t, int, int, const float *, int64_t,
-                                                   const float *, int64_t, double *, double *,
-                                                   hipStream_t);
+                                                   const float *, int64_t, int, double *,
+                                                   double *, hipStream_t);
 template hipError_t launch_gram_wide<double, float>(int64_t, int, int, const double *, int64_t,
-                                                    const float *, int64_t, double *, double *,
-                                                    hipStream_t);
+                                                    const float *, int64_t, int, double *,
+                                                    double *, hipStream_t);
 
 hipError_t launch_chol_solve_wide(int n, int nrhs, int nc, double *W, const double *fact,
                                   int64_t ldf, double *X, int64_t ldx, double *R, int64_t ldr,
