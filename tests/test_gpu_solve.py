@@ -496,3 +496,46 @@ def test_refinement_last_rows(ms, d, n, nrhs, dtype):
     X0, ws0 = ms.sketch_lstsq(A, B, h, s, G, k, mode="sorted", refine_steps=2)
     ms.check_status(ws0)
     assert torch.isfinite(X).all() and torch.equal(X, X0)
+
+
+# Refinement in the deterministic mode: the keys are made for the sketch's n + nrhs columns
+# and folded once more, in FP64, for the nrhs columns of the residual.  Slices of one, two and
+# four buckets, 20- to 138-column sketches whose keys are not sliced although those of
+# nrhs columns alone would be, fewer blocks than two slices a thread are used for, few buckets,
+# uneven blocks, and rows that are no multiple of a block.
+#
+# FP64: X is the sketch-and-solve solution and stays there (1e-12, the bar of
+# test_lstsq_fp64_parity): a wrong sketch of the residual moves it by
+# about the noise / |x| * sqrt(n / k2), 1e-4 and more.  FP32 data: the rounding of the sketch and
+# of the FP32 product perturbs Z by at most sqrt(k) 2^-24 < 1e-5 relative; the fixed
+# point is off by that times kappa(Z_A)^2 <= 9 times the sketched residual over |A x|, at most
+# 1e-2, i.e. below 1e-6, and a step reduces what is above it by 9e-5.
+SORTED_KEYS = [(20001, 8, 2, 100), (20001, 8, 3, 4096), (30003, 8, 1, 5000), (30003, 16, 2, 8192),
+               (9001, 20, 1, 9000), (50001, 20, 4, 16384), (20001, 100, 2, 10000),
+               (5001, 126, 2, 16384), (30001, 130, 2, 4096), (30001, 136, 2, 8192),
+               (30001, 132, 1, 16384), (12289, 4, 2, 31)]
+
+
+# (runs of 64 rows to a bucket: where enough buckets hold a row for the rank)
+@pytest.mark.parametrize("d,n,nrhs,k,runs", [c + (False,) for c in SORTED_KEYS] +
+                         [c + (True,) for c in SORTED_KEYS if c[0] >= 256 * c[1]])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_refinement_sorted_keys(ms, orc, d, n, nrhs, k, runs, dtype):
+    print("refine sorted d=%d n=%d nrhs=%d k=%d runs=%d %s" % (d, n, nrhs, k, runs, dtype),
+          flush=True)
+    k2 = 4 * n
+    rng = np.random.default_rng(d + n + k)
+    npdt = np.float32 if dtype == torch.float32 else np.float64
+    A = np.asfortranarray(rng.standard_normal((d, n)), dtype=npdt)
+    B = A @ rng.standard_normal((n, nrhs)) + 1e-2 * rng.standard_normal((d, nrhs))
+    B = np.asfortranarray(B, dtype=npdt)
+    h = (rng.permutation(k)[np.arange(d) // 64 % k] if runs else rng.integers(0, k, d))
+    h = h.astype(np.int32)
+    s = (2 * rng.integers(0, 2, d) - 1).astype(np.int8)
+    G = (rng.standard_normal((k2, k)) / k2 ** 0.5).astype(npdt)
+    Xr = orc.sketch_lstsq(A.astype(np.float64), B.astype(np.float64), h, s,
+                          G.astype(np.float64), k)[0]
+    for steps in (1, 2):
+        X = _gpu_lstsq(ms, A, B, h, s, G, k, gd="f64" if npdt == np.float64 else "f32",
+                       mode="sorted", refine_steps=steps)
+        assert rel(X, Xr) <= (1e-12 if npdt == np.float64 else 1e-6)
