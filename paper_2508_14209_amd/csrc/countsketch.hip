@@ -22,12 +22,12 @@ namespace ms {
 
 // ------------------------------------------------------------------ helpers
 
-__global__ void k_zero_status(int *status) {
-  if (threadIdx.x == 0) *status = MS_OK;
+__global__ void k_zero_status(int *status, int words) {
+  if ((int)threadIdx.x < words) status[threadIdx.x] = MS_OK;
 }
 
-hipError_t launch_zero_status(int *status, hipStream_t st) {
-  hipLaunchKernelGGL(k_zero_status, dim3(1), dim3(64), 0, st, status);
+hipError_t launch_zero_status(int *status, hipStream_t st, int words) {
+  hipLaunchKernelGGL(k_zero_status, dim3(1), dim3(64), 0, st, status, words);
   return hipGetLastError();
 }
 

@@ -22,6 +22,7 @@
 // and every thread walks the entries of its own buckets with their sums in
 // registers (k_bf_fold_sliced).
 #include <algorithm>
+#include <type_traits>
 
 #include "ms_internal.h"
 
@@ -132,7 +133,8 @@ template <bool SLICED>
 __global__ __launch_bounds__(kBfT) void k_bf_keys_count(int64_t d, int k,
                                                         const int32_t *__restrict__ h,
                                                         const int8_t *__restrict__ s,
-                                                        uint32_t *__restrict__ keys, int *status) {
+                                                        uint32_t *__restrict__ keys, int *status,
+                                                        int *uneven) {
   extern __shared__ __align__(16) uint32_t bsm[];
   __shared__ uint32_t wsum[kBfT / 64];
   __shared__ int s_long, s_uneven;
@@ -154,16 +156,17 @@ __global__ __launch_bounds__(kBfT) void k_bf_keys_count(int64_t d, int k,
   __syncthreads();
   // exclusive scan of the k + 1 counts, thread t owning a contiguous range
   const int per = (k + 1 + kBfT - 1) / kBfT;
-  const uint32_t most = bf_even_rows(k);
-  uint32_t loc = 0;
+  uint32_t loc = 0, most = 0;
   for (int q = 0; q < per; ++q) {
     const int m = tid * per + q;
     if (m <= k) {
-      loc += cnt[m];
-      if (cnt[m] > (uint32_t)kBfCountMaxRun && m < k) atomicOr(&s_long, 1);
-      if (SLICED && cnt[m] > most && m < k) s_uneven = 1;
+      const uint32_t n = cnt[m];
+      loc += n;
+      most = max(most, m < k ? n : 0u);
     }
   }
+  if (most > (uint32_t)kBfCountMaxRun) s_long = 1;
+  if (SLICED && most > bf_even_rows(k)) s_uneven = 1;
   uint32_t incl = loc;
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
@@ -176,6 +179,7 @@ __global__ __launch_bounds__(kBfT) void k_bf_keys_count(int64_t d, int k,
   // thread t's sorted keys 4t .. 4t + 3, as keys or as 16-bit entries
   const int nb = SLICED ? bf_slice_buckets(k) : 1;
   const bool sliced = SLICED && !s_uneven;
+  if (SLICED && !sliced && tid == 0) *uneven = 1;
   auto store = [&]() {
     if (sliced) {
       uint32_t e[4];
@@ -407,13 +411,14 @@ __global__ __launch_bounds__(kBfT) void k_bf_fold(int64_t d, int k, Cols<T> cols
 // Bound by what one compute unit reads from its L2 (every part reads the whole
 // column, about 30 bytes a cycle: 1.0 of the 1.4 ms below) and then by the walk,
 // in which a wave takes as many steps as the longest of its 64 slices (4 to 5
-// where they average one).  4,194,304 x 65 FP64, k = 8192: 1.37 ms against 2.06
+// where they average one).  4,194,304 x 65 FP64, k = 8192: 1.39 ms against 2.06
 // for bf_fold_column, whose threads own positions instead (every thread
 // looks at every position of its four, reads and writes the sums in LDS).
 // Uneven blocks leave that loop (their second halves in flight with the rest cost the even
 // ones a tenth): they, and even ones until kSlCalm follow each other, are staged one block
 // ahead and folded with the sums in LDS.  1,000,003 x 65 FP64, k = 16,384, 64 rows in a row
-// to a bucket: 0.78 ms, 2.9 walked, 0.84 by bf_fold_column.
+// to a bucket: 0.79 ms, 2.9 walked, 0.85 by bf_fold_column.  The loop looks for uneven blocks only
+// where the keys' pass met one (*uneven): looking costs it 2 to 3 % (1.42 and 1.44 ms).
 constexpr int kSlAhead = 4, kSlCalm = 8;
 
 // An uneven block, staged in sg (values) and kg (sorted keys), into acc (slot m - m0 of
@@ -461,6 +466,7 @@ template <typename T, int B, int NS>
 __global__ __launch_bounds__(kBfT) void k_bf_fold_sliced(int64_t d, int k, Cols<T> cols, int parts,
                                                          int xcds,
                                                          const uint32_t *__restrict__ keys,
+                                                         const int *__restrict__ uneven,
                                                          T *__restrict__ Y, int64_t ldy) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   // (the entries first: the one past a buffer's end is read, not used)
@@ -500,7 +506,9 @@ __global__ __launch_bounds__(kBfT) void k_bf_fold_sliced(int64_t d, int k, Cols<
   const T *cb;
   const uint32_t *kb;
   int fb;
-  auto values_at = [&](int b) { return b < nblk - 1 ? col + (int64_t)b * kBfRows : col + (d - kBfRows); };
+  auto values_at = [&](int b) {
+    return b < nblk - 1 ? col + (int64_t)b * kBfRows : col + (d - kBfRows);
+  };
   auto load_values = [&](const T *from, V (&to)[kV]) {
 #pragma unroll
     for (int q = 0; q < kV; ++q)
@@ -565,99 +573,106 @@ __global__ __launch_bounds__(kBfT) void k_bf_fold_sliced(int64_t d, int k, Cols<
   };
   const int q4 = tid & 3;
   static_assert(kSlAhead == 4, "buffers and slots of the unrolled loop");
-  for (int b = 0; b < nblk;) {
-    uint32_t word = tell(b + q4);
-    fb = b;
-    cb = values_at(b);
-    kb = keys + (int64_t)b * kBfRows;
-#pragma unroll
-    for (int j = 0; j < kSlAhead; ++j) fetch(j);
-    bool odd = __any(word & kBfUneven);   // one of the next four blocks
-    if (!odd) {
-      put(0, 0);
-#pragma unroll
-      for (int n = 0; n < NS; ++n) {
-        cl[n] = lo[0][n];
-        ch[n] = hi[0][n];
-      }
-      fetch(0);
-      __syncthreads();
-    }
-    while (b < nblk && !odd) {
-      word = tell(b + kSlAhead + q4);
-#pragma unroll
-      for (int j = 0; j < kSlAhead; ++j) {
-        if (b >= nblk) break;
-        constexpr int kNext[kSlAhead] = {1, 2, 3, 0};
-        const int jn = kNext[j], cur = j & 1;
-        uint16_t nl[NS], nh[NS];
-        put(jn, cur ^ 1);   // (after the last block: a block that is not folded)
-#pragma unroll
+  // UNEVEN: some block of the matrix is
+  auto blocks = [&](auto UNEVEN) {
+    for (int b = 0; b < nblk;) {
+      uint32_t word = UNEVEN ? tell(b + q4) : 0u;
+      fb = b;
+      cb = values_at(b);
+      kb = keys + (int64_t)b * kBfRows;
+  #pragma unroll
+      for (int j = 0; j < kSlAhead; ++j) fetch(j);
+      bool odd = UNEVEN && __any(word & kBfUneven);   // one of the next four blocks
+      if (!odd) {
+        put(0, 0);
+  #pragma unroll
         for (int n = 0; n < NS; ++n) {
-          nl[n] = lo[jn][n];
-          nh[n] = hi[jn][n];
+          cl[n] = lo[0][n];
+          ch[n] = hi[0][n];
         }
-        fetch(jn);
-        fold(stage + cur * kBfRows + (b + 1 < nblk ? 0 : shift), lent + cur * kBfRows);
-#pragma unroll
-        for (int n = 0; n < NS; ++n) {
-          cl[n] = nl[n];
-          ch[n] = nh[n];
-        }
-        __syncthreads();   // this block folded, the next one staged
-        ++b;
+        fetch(0);
+        __syncthreads();
       }
-      odd = __any(word & kBfUneven);
-    }
-    if (b >= nblk) break;
-    // four blocks with an uneven one among them: the sums in LDS (slot: bucket of this part)
-#pragma unroll
-    for (int n = 0; n < NS; ++n)
-#pragma unroll
-      for (int q = 0; q < B; ++q)
-        if (s0 + tid + kBfT * n < s1) lacc[(sl[n] - s0) * B + q] = acc[n][q];
-    V cv[kV];
-    bf_u32x4 ck;
-    uint32_t ct;
-    uint32_t *lkey = reinterpret_cast<uint32_t *>(lent);
-    auto ahead = [&](int at) {
-      ct = tell(at);
-      load_values(values_at(at), cv);
-      ck = gload(reinterpret_cast<const bf_u32x4 *>(keys + (int64_t)at * kBfRows) + tid);
-    };
-    ahead(b);
-    for (int calm = 0; b < nblk && calm < kSlCalm; ++b) {
-      put_values(cv, stage);
-      const bool unb = (__builtin_amdgcn_readfirstlane(ct) & kBfUneven) != 0;
-      if (unb && tid == kBfRows / 2 / 4 && ck[0] != kBfPad) ck[0] &= ~kBfUneven;
-      *reinterpret_cast<bf_u32x4 *>(lkey + 4 * tid) = ck;
-      __syncthreads();
-      ahead(min(b + 1, nblk - 1));
-      const T *sg = stage + (b + 1 < nblk ? 0 : shift);
-      if (unb) {
-        bf_fold_uneven(sg, lkey, (uint32_t)(s0 * B), (uint32_t)min(s1 * B, k), lacc);
-      } else {
-        const uint16_t *ends = lent + kBfRows;
-#pragma unroll 1
-        for (int s = s0 + tid; s < s1; s += kBfT) {
-          T sums[B];
-#pragma unroll
-          for (int q = 0; q < B; ++q) sums[q] = lacc[(s - s0) * B + q];
-          walk(reinterpret_cast<const unsigned char *>(sg),
-               reinterpret_cast<const unsigned char *>(lent), s > 0 ? 2u * ends[s - 1] : 0u,
-               2u * ends[s], sums);
-#pragma unroll
-          for (int q = 0; q < B; ++q) lacc[(s - s0) * B + q] = sums[q];
+      while (b < nblk && !odd) {
+        if (UNEVEN) word = tell(b + kSlAhead + q4);
+  #pragma unroll
+        for (int j = 0; j < kSlAhead; ++j) {
+          if (b >= nblk) break;
+          constexpr int kNext[kSlAhead] = {1, 2, 3, 0};
+          const int jn = kNext[j], cur = j & 1;
+          uint16_t nl[NS], nh[NS];
+          put(jn, cur ^ 1);   // (after the last block: a block that is not folded)
+  #pragma unroll
+          for (int n = 0; n < NS; ++n) {
+            nl[n] = lo[jn][n];
+            nh[n] = hi[jn][n];
+          }
+          fetch(jn);
+          fold(stage + cur * kBfRows + (b + 1 < nblk ? 0 : shift), lent + cur * kBfRows);
+  #pragma unroll
+          for (int n = 0; n < NS; ++n) {
+            cl[n] = nl[n];
+            ch[n] = nh[n];
+          }
+          __syncthreads();   // this block folded, the next one staged
+          ++b;
         }
+        odd = UNEVEN && __any(word & kBfUneven);
       }
-      calm = unb ? 0 : calm + 1;
-      __syncthreads();
+      if (!UNEVEN || b >= nblk) break;
+      // four blocks with an uneven one among them: the sums in LDS (slot: bucket of this part)
+  #pragma unroll
+      for (int n = 0; n < NS; ++n)
+  #pragma unroll
+        for (int q = 0; q < B; ++q)
+          if (s0 + tid + kBfT * n < s1) lacc[(sl[n] - s0) * B + q] = acc[n][q];
+      V cv[kV];
+      bf_u32x4 ck;
+      uint32_t ct;
+      uint32_t *lkey = reinterpret_cast<uint32_t *>(lent);
+      auto ahead = [&](int at) {
+        ct = tell(at);
+        load_values(values_at(at), cv);
+        ck = gload(reinterpret_cast<const bf_u32x4 *>(keys + (int64_t)at * kBfRows) + tid);
+      };
+      ahead(b);
+      for (int calm = 0; b < nblk && calm < kSlCalm; ++b) {
+        put_values(cv, stage);
+        const bool unb = (__builtin_amdgcn_readfirstlane(ct) & kBfUneven) != 0;
+        if (unb && tid == kBfRows / 2 / 4 && ck[0] != kBfPad) ck[0] &= ~kBfUneven;
+        *reinterpret_cast<bf_u32x4 *>(lkey + 4 * tid) = ck;
+        __syncthreads();
+        ahead(min(b + 1, nblk - 1));
+        const T *sg = stage + (b + 1 < nblk ? 0 : shift);
+        if (unb) {
+          bf_fold_uneven(sg, lkey, (uint32_t)(s0 * B), (uint32_t)min(s1 * B, k), lacc);
+        } else {
+          const uint16_t *ends = lent + kBfRows;
+  #pragma unroll 1
+          for (int s = s0 + tid; s < s1; s += kBfT) {
+            T sums[B];
+  #pragma unroll
+            for (int q = 0; q < B; ++q) sums[q] = lacc[(s - s0) * B + q];
+            walk(reinterpret_cast<const unsigned char *>(sg),
+                 reinterpret_cast<const unsigned char *>(lent), s > 0 ? 2u * ends[s - 1] : 0u,
+                 2u * ends[s], sums);
+  #pragma unroll
+            for (int q = 0; q < B; ++q) lacc[(s - s0) * B + q] = sums[q];
+          }
+        }
+        calm = unb ? 0 : calm + 1;
+        __syncthreads();
+      }
+  #pragma unroll
+      for (int n = 0; n < NS; ++n)
+  #pragma unroll
+        for (int q = 0; q < B; ++q) acc[n][q] = lacc[(sl[n] - s0) * B + q];
     }
-#pragma unroll
-    for (int n = 0; n < NS; ++n)
-#pragma unroll
-      for (int q = 0; q < B; ++q) acc[n][q] = lacc[(sl[n] - s0) * B + q];
-  }
+  };
+  if (*uneven)
+    blocks(std::true_type{});
+  else
+    blocks(std::false_type{});
 #pragma unroll
   for (int n = 0; n < NS; ++n)
     if (s0 + tid + kBfT * n < s1)
@@ -814,7 +829,7 @@ bool cs_blockfold_sliced(int64_t d, int64_t k, int64_t ncols) {
 }
 
 hipError_t launch_bf_keys(int64_t d, int64_t k, const int32_t *h, const int8_t *s, uint32_t *keys,
-                          bool sliced, int *status, hipStream_t st) {
+                          bool sliced, int *status, int *uneven, hipStream_t st) {
   if (d < 1 || k < 1 || k > kBfMaxK || (sliced && k > kBfCountMaxK)) return hipErrorInvalidValue;
   const int64_t nblk = (d + kBfRows - 1) / kBfRows;
   if (k <= kBfCountMaxK) {
@@ -824,10 +839,10 @@ hipError_t launch_bf_keys(int64_t d, int64_t k, const int32_t *h, const int8_t *
     if (e != hipSuccess) return e;
     if (sliced)
       hipLaunchKernelGGL(k_bf_keys_count<true>, dim3((unsigned)nblk), dim3(kBfT), lds, st, d,
-                         (int)k, h, s, keys, status);
+                         (int)k, h, s, keys, status, uneven);
     else
       hipLaunchKernelGGL(k_bf_keys_count<false>, dim3((unsigned)nblk), dim3(kBfT), lds, st, d,
-                         (int)k, h, s, keys, status);
+                         (int)k, h, s, keys, status, uneven);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(k_bf_keys, dim3((unsigned)nblk), dim3(kBfT), 0, st, d, (int)k, h, s, keys,
@@ -837,20 +852,21 @@ hipError_t launch_bf_keys(int64_t d, int64_t k, const int32_t *h, const int8_t *
 
 template <typename T, int B, int NS>
 static hipError_t launch_bf_sliced(int64_t d, int64_t k, const Cols<T> &c, int parts,
-                                   const uint32_t *keys, T *Y, int64_t ldy, hipStream_t st) {
+                                   const uint32_t *keys, const int *uneven, T *Y, int64_t ldy,
+                                   hipStream_t st) {
   constexpr size_t lds = (size_t)2 * kBfRows * (sizeof(T) + 2) + (size_t)NS * kBfT * B * sizeof(T);
   hipError_t e = allow_dynamic_lds((const void *)k_bf_fold_sliced<T, B, NS>, (int)lds);
   if (e != hipSuccess) return e;
   const int xcds = std::max(1, dev_info().xcds);
   hipLaunchKernelGGL((k_bf_fold_sliced<T, B, NS>),
                      dim3((unsigned)((c.ncols + xcds - 1) / xcds * xcds * parts)), dim3(kBfT), lds,
-                     st, d, (int)k, c, parts, xcds, keys, Y, ldy);
+                     st, d, (int)k, c, parts, xcds, keys, uneven, Y, ldy);
   return hipGetLastError();
 }
 
 template <typename T>
 hipError_t launch_bf_fold(int64_t d, int64_t k, const Cols<T> &c, const uint32_t *keys,
-                          bool sliced, T *Y, int64_t ldy, hipStream_t st) {
+                          bool sliced, const int *uneven, T *Y, int64_t ldy, hipStream_t st) {
   if (sliced) {
     // (the residuals' fold has fewer columns than the keys were chosen for)
     if (!cs_blockfold_sliced(d, k, c.ncols)) return hipErrorInvalidValue;
@@ -860,8 +876,8 @@ hipError_t launch_bf_fold(int64_t d, int64_t k, const Cols<T> &c, const uint32_t
     const bool one = (nsl + parts - 1) / parts <= kBfT;   // slices per thread: 1 or 2
 #define MS_SLICED(B_)                                                                          \
   if (B == B_)                                                                                 \
-    return one ? launch_bf_sliced<T, B_, 1>(d, k, c, parts, keys, Y, ldy, st)                  \
-               : launch_bf_sliced<T, B_, 2>(d, k, c, parts, keys, Y, ldy, st);
+    return one ? launch_bf_sliced<T, B_, 1>(d, k, c, parts, keys, uneven, Y, ldy, st)          \
+               : launch_bf_sliced<T, B_, 2>(d, k, c, parts, keys, uneven, Y, ldy, st);
     MS_SLICED(1) MS_SLICED(2) MS_SLICED(4)
 #undef MS_SLICED
   }
@@ -920,8 +936,9 @@ template hipError_t launch_batch_bf_fold<double, 1>(int, const ms_problem *, con
                                                     hipStream_t);
 
 template hipError_t launch_bf_fold<double>(int64_t, int64_t, const Cols<double> &,
-                                           const uint32_t *, bool, double *, int64_t, hipStream_t);
+                                           const uint32_t *, bool, const int *, double *, int64_t,
+                                           hipStream_t);
 template hipError_t launch_bf_fold<float>(int64_t, int64_t, const Cols<float> &, const uint32_t *,
-                                          bool, float *, int64_t, hipStream_t);
+                                          bool, const int *, float *, int64_t, hipStream_t);
 
 }  // namespace ms

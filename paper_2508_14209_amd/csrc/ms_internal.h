@@ -99,7 +99,8 @@ struct Cols {
 };
 
 // countsketch.hip
-hipError_t launch_zero_status(int *status, hipStream_t st);
+// words: 2 also clears the word after it (launch_bf_keys's uneven flag).
+hipError_t launch_zero_status(int *status, hipStream_t st, int words = 1);
 // Clear the status word and a rows x cols buffer (ld) in one launch.
 template <typename T>
 hipError_t launch_prologue(int *status, T *Y, int64_t rows, int64_t cols, int64_t ld,
@@ -672,12 +673,13 @@ bool cs_blockfold_supported(int64_t d, int64_t k, int ncols, size_t elem);
 size_t cs_blockfold_key_bytes(int64_t d);
 // The keys of a call that folds at most ncols columns at a time: sliced (16-bit
 // entries grouped for one fold thread per few buckets) or 32-bit; the same
-// value goes to the keys and to every fold of them.
+// value goes to the keys and to every fold of them.  uneven: a cleared word, set
+// where a sliced block keeps 32-bit keys; the folds read it.
 bool cs_blockfold_sliced(int64_t d, int64_t k, int64_t ncols);
 hipError_t launch_bf_keys(int64_t d, int64_t k, const int32_t *h, const int8_t *s, uint32_t *keys,
-                          bool sliced, int *status, hipStream_t st);
+                          bool sliced, int *status, int *uneven, hipStream_t st);
 template <typename T>
 hipError_t launch_bf_fold(int64_t d, int64_t k, const Cols<T> &c, const uint32_t *keys,
-                          bool sliced, T *Y, int64_t ldy, hipStream_t st);
+                          bool sliced, const int *uneven, T *Y, int64_t ldy, hipStream_t st);
 
 }  // namespace ms

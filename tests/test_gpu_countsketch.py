@@ -402,6 +402,23 @@ def test_sorted_uneven_blocks(ms, orc, pattern, n, k, dt):
     assert bits_equal(to_host(Y), np.asfortranarray(orc.countsketch(A, h, s, k)))
 
 
+# One workspace, its old contents all ones, for an even, an uneven and again an even map: what
+# a call finds out about its blocks is not left to the next one.  Bit-exact.
+def test_sorted_uneven_workspace_again(ms, orc):
+    d, n, k = 20000, 9, 8192
+    print("uneven workspace again", flush=True)
+    A, s = synth.normal_matrix(d, n, seed=5), synth.signs(d, seed=6)
+    h = synth.bucket_map(d, k, seed=7)
+    u = h.copy()
+    u[9000:9900] = 77
+    ws = ms.workspace(ms.workspace_size("countsketch", d=d, n=n, k=k, mode="sorted"))
+    ws.fill_(255)
+    for hh in (h, u, h, u):
+        Y, _ = ms.countsketch_apply(to_dev(A), to_dev(hh), to_dev(s), k, mode="sorted", ws=ws)
+        ms.check_status(ws)
+        assert bits_equal(to_host(Y), np.asfortranarray(orc.countsketch(A, hh, s, k)))
+
+
 # Two slices a thread: the row counts around which they are taken (16,384 for two
 # buckets a slice, 49,152 for four), beside one slice at the same sizes.  Bit-exact.
 @pytest.mark.parametrize("d", [16383, 16384, 49151, 49152])
