@@ -301,7 +301,7 @@ hipError_t run_countsketch(int64_t d, int64_t k, const Cols<T> &c, const int32_t
   if (mode == MS_CS_SORTED && L.bkeys_bytes) {
     int *uneven = status + 1;   // (the status word's 256 bytes)
     e = launch_zero_status(status, st, 2);
-    const bool sl = cs_blockfold_sliced(d, k, c.ncols);
+    const bool sl = cs_blockfold_sliced(d, k, c.ncols, sizeof(T));
     uint32_t *keys = at<uint32_t>(ws, L.bkeys);
     if (e == hipSuccess) e = launch_bf_keys(d, k, h, s, keys, sl, status, uneven, st);
     if (e == hipSuccess) e = launch_bf_fold<T>(d, k, c, keys, sl, uneven, Y, ldy, st);
@@ -705,8 +705,8 @@ ms_status sketch_lstsq(int64_t d, int64_t n, int64_t nrhs, int64_t k, int64_t k2
     Cols<double> cr{r, d, nullptr, 0, (int)nrhs, (int)nrhs};
     if (mode == MS_CS_SORTED && L.cs.bkeys_bytes)
       e = launch_bf_fold<double>(d, k, cr, at<uint32_t>(ws, L.cs.bkeys),
-                                 cs_blockfold_sliced(d, k, nc), status + 1, at<double>(ws, L.yr),
-                                 k, st);
+                                 cs_blockfold_sliced(d, k, nc, dtype_size(a_dtype)), status + 1,
+                                 at<double>(ws, L.yr), k, st);
     else if (mode == MS_CS_SORTED)
       e = launch_cs_sorted_cols<double>(k, cr, at<int32_t>(ws, L.cs.off), at<uint32_t>(ws, L.cs.sperm),
                                    at<double>(ws, L.yr), k, st);

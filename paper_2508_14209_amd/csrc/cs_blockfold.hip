@@ -811,6 +811,12 @@ int bf_sliced_parts(int ncols) {
   return std::max(1, std::min(16, di.cus / xcds / per));
 }
 
+// Slices of a part.
+int64_t bf_sliced_own(int64_t k, int ncols) {
+  const int64_t B = bf_slice_buckets(k), nsl = (k + B - 1) / B, parts = bf_sliced_parts(ncols);
+  return (nsl + parts - 1) / parts;
+}
+
 }  // namespace
 
 // Sliced keys are used where a fold thread then owns at most two slices (up
@@ -819,13 +825,13 @@ int bf_sliced_parts(int ncols) {
 // k = 8192) 3.3 against 2.4.  Two slices of two or four buckets each take longer to clear,
 // walk and store, and need a few blocks to make up for it: 5000 x 128, k = 16,384:
 // 33.8 us against 30.7, 20,000 x 100, k = 10,000: 34 and 33, 100,003 x 128: 76 and 82; k = 8192:
-// 5000 x 128 29 and 27.6, 20,000 x 128 31 and 35.  Fewer than 32 buckets (chains of more
+// 5000 x 128 29 and 27.6, 20,000 x 128 31 and 35.  FP32 sooner: k = 16,384, 20,001 x 128 33.6 and
+// 36.0, x 65 30.5 and 35.0; 5000 x 128 30.1 and 28.2.  Fewer than 32 buckets (chains of more
 // than 128 rows a block) keep the keys too.
-bool cs_blockfold_sliced(int64_t d, int64_t k, int64_t ncols) {
+bool cs_blockfold_sliced(int64_t d, int64_t k, int64_t ncols, size_t elem) {
   if (d < kBfRows || k < kBfSliceMinK || k > kBfCountMaxK || ncols < 1 || ncols > 65535) return false;
-  const int64_t B = bf_slice_buckets(k), nsl = (k + B - 1) / B, parts = bf_sliced_parts((int)ncols);
-  const int64_t own = (nsl + parts - 1) / parts;   // slices of a part
-  return own <= kBfT || (own <= 2 * kBfT && d >= (B - 1) * 4 * kBfRows);
+  const int64_t B = bf_slice_buckets(k), own = bf_sliced_own(k, (int)ncols);
+  return own <= kBfT || (own <= 2 * kBfT && d >= (B - 1) * (elem == 8 ? 4 : 1) * kBfRows);
 }
 
 hipError_t launch_bf_keys(int64_t d, int64_t k, const int32_t *h, const int8_t *s, uint32_t *keys,
@@ -868,8 +874,11 @@ template <typename T>
 hipError_t launch_bf_fold(int64_t d, int64_t k, const Cols<T> &c, const uint32_t *keys,
                           bool sliced, const int *uneven, T *Y, int64_t ldy, hipStream_t st) {
   if (sliced) {
-    // (the residuals' fold has fewer columns than the keys were chosen for)
-    if (!cs_blockfold_sliced(d, k, c.ncols)) return hipErrorInvalidValue;
+    // (the residuals' fold has fewer columns than the keys were chosen for,
+    // and FP64 ones where the data may be FP32)
+    if (d < kBfRows || k < kBfSliceMinK || k > kBfCountMaxK || c.ncols < 1 ||
+        bf_sliced_own(k, c.ncols) > 2 * kBfT)
+      return hipErrorInvalidValue;
     const int B = bf_slice_buckets(k);
     const int nsl = (int)((k + B - 1) / B);
     const int parts = std::min(bf_sliced_parts(c.ncols), nsl);

@@ -671,11 +671,12 @@ hipError_t launch_batch_bf_fold(int count, const ms_problem *P, const BatchEntry
 // blocks in order with its bucket sums in LDS (elem: bytes of the data type).
 bool cs_blockfold_supported(int64_t d, int64_t k, int ncols, size_t elem);
 size_t cs_blockfold_key_bytes(int64_t d);
-// The keys of a call that folds at most ncols columns at a time: sliced (16-bit
+// The keys of a call that folds at most ncols columns of elem-byte data (and, later,
+// fewer FP64 ones of the same sketch) at a time: sliced (16-bit
 // entries grouped for one fold thread per few buckets) or 32-bit; the same
 // value goes to the keys and to every fold of them.  uneven: a cleared word, set
 // where a sliced block keeps 32-bit keys; the folds read it.
-bool cs_blockfold_sliced(int64_t d, int64_t k, int64_t ncols);
+bool cs_blockfold_sliced(int64_t d, int64_t k, int64_t ncols, size_t elem);
 hipError_t launch_bf_keys(int64_t d, int64_t k, const int32_t *h, const int8_t *s, uint32_t *keys,
                           bool sliced, int *status, int *uneven, hipStream_t st);
 template <typename T>

@@ -432,6 +432,18 @@ def test_sorted_two_slices_rows(ms, orc, d, n, k):
     assert bits_equal(to_host(Y), np.asfortranarray(orc.countsketch(A, h, s, k)))
 
 
+# FP32: from 4096 rows for two buckets a slice, 12,288 for four.  Bit-exact.
+@pytest.mark.parametrize("d", [4096, 12287, 12288])
+@pytest.mark.parametrize("n,k", [(66, 8192), (66, 16384), (128, 10000)])
+def test_sorted_two_slices_rows_f32(ms, orc, d, n, k):
+    print("two slices f32 d=%d n=%d k=%d" % (d, n, k), flush=True)
+    A = synth.normal_matrix(d, n, seed=d + k, dtype=np.float32)
+    h, s = synth.bucket_map(d, k, seed=d), synth.signs(d, seed=d + 1)
+    Y, ws = ms.countsketch_apply(to_dev(A), to_dev(h), to_dev(s), k, mode="sorted")
+    ms.check_status(ws)
+    assert bits_equal(to_host(Y), np.asfortranarray(orc.countsketch(A, h, s, k)))
+
+
 def test_sorted_slices_special_values(ms, orc):
     # infinities, NaN, signed zeros and the smallest subnormal keep their bits
     # (a thread adds +0.0 to the sums of its other buckets)
