@@ -411,8 +411,8 @@ __global__ __launch_bounds__(kBfT) void k_bf_fold(int64_t d, int k, Cols<T> cols
 // Bound by what one compute unit reads from its L2 (every part reads the whole
 // column, about 30 bytes a cycle: 1.0 of the 1.4 ms below) and then by the walk,
 // in which a wave takes as many steps as the longest of its 64 slices (4 to 5
-// where they average one).  4,194,304 x 65 FP64, k = 8192: 1.39 ms against 2.06
-// for bf_fold_column, whose threads own positions instead (every thread
+// where they average one).  4,194,304 x 65 FP64, k = 8192, the keys included: 1.41 ms against
+// 2.09 for bf_fold_column, whose threads own positions instead (every thread
 // looks at every position of its four, reads and writes the sums in LDS).
 // Uneven blocks leave that loop (their second halves in flight with the rest cost the even
 // ones a tenth): they, and even ones until kSlCalm follow each other, are staged one block
@@ -821,7 +821,7 @@ int64_t bf_sliced_own(int64_t k, int ncols) {
 
 // Sliced keys are used where a fold thread then owns at most two slices (up
 // to 128 columns, and more for few buckets): 4,194,304 x 65 FP64, k = 8192:
-// 1.44 ms against 2.08 for positions; with four slices a thread (129 columns,
+// 1.41 ms against 2.09 for positions; with four slices a thread (129 columns,
 // k = 8192) 3.3 against 2.4.  Two slices of two or four buckets each take longer to clear,
 // walk and store, and need a few blocks to make up for it: 5000 x 128, k = 16,384:
 // 33.8 us against 30.7, 20,000 x 100, k = 10,000: 34 and 33, 100,003 x 128: 76 and 82; k = 8192:

@@ -69,7 +69,7 @@ TileShape tile_shape(int64_t d, int64_t k) {
   int nbt = 2;
   while (nbt < need) nbt *= 2;
   // two bucket tiles: the untiled kernel, whose two tiles each stream every
-  // row, measured faster (16,777,216 x 129 FP32, k = 32,768: 2.67 vs 4.2 ms);
+  // row, measured faster (16,777,216 x 129 FP32, k = 32,768: 2.46 vs 4.2 ms);
   // from four tiles the per-tile entry lists win (k = 131,072: 4.3 vs 7.9 ms)
   if (nbt < 4 || nbt > kMaxTiles) return s;
   s.nbt = nbt;
@@ -375,9 +375,11 @@ hipError_t launch_cs_tiled(int64_t d, int64_t k, const Cols<T> &c, const void *p
                        c, k, sh.ktile, sh.nbt, sh.nblk, ent, boff, xcds, subs, Y, ldy);
     return hipGetLastError();
   };
-  // 64 W E entries hold a list of 7680 / nbt on average and two deviations; the
-  // fewer waves to a block the better (8 tiles, FP32 as above: 16 waves 4.7, 8 waves
-  // 4.5, 4 waves 4.3 ms), up to four entries a lane (2 waves, 8 entries: 4.5 ms;
+  // 64 W E entries hold a list of kBlk / nbt on average and, with 4 and 8 tiles, 3.4 and
+  // 2.2 deviations; with 16 (512 for 480 and a deviation of 21) and 32 tiles (256 for 240
+  // and 15) 1.5 and one: there about one list in 15 and in 7 has a remainder, which is
+  // read after the rest.  The fewer waves to a block the better (8 tiles, FP32 as
+  // above: 16 waves 4.7, 8 waves 4.5, 4 waves 4.3 ms), up to four entries a lane (2 waves, 8 entries: 4.5 ms;
   // with 4 tiles all measured alike)
   switch (sh.nbt) {
     case 4: return go(k_cs_tiled<T, 16, 2>);

@@ -15,13 +15,18 @@
 // the current one is multiplied), laid out so that staging writes and fragment
 // reads are both contiguous 16-byte accesses.  The tiles are dealt out to the
 // waves in row-major runs of equal length (at most 20 accumulator tiles, 160
-// registers a lane).  Where fewer than eight waves hold all the
-// tiles (n + nrhs <= 192), two or four groups of waves each take their own 16
-// rows of a taller slab.  Every group writes its sums as packed tiles; an
+// of a lane's 256 registers).  With the fragments, the staged slab and its pointers
+// that is more than there are for 8, 12 and 17 tile columns in FP64 (13, 22 and 12
+// registers spilled, reloaded once a slab) and 12 and 17 in FP32 (8 and 1).  FP64 Q0
+// beside FP32 B (rand_cholQR of FP32 data; 22 to 43 spilled at 8, 11, 12 and 17)
+// loads and converts B's few columns one element at a time, so that each slab
+// waits for them; it is not slower for it than the pass before was.  Where
+// fewer than eight waves hold all the tiles (n + nrhs <= 192), two or four groups
+// of waves each take their own 16 rows of a taller slab.  Every group writes its sums as packed tiles; an
 // ordered pass adds them (the same bits on every run).
-// 4,194,304 x 256 FP64, one right-hand side: 20.9 -> 6.2 ms (55 TFLOP/s executed
-// of the instruction's 77); 2 x 4-tile tasks per wave, which re-read V from L2
-// and waited for each slab's loads, were what it took before.
+// 4,194,304 x 256 FP64, one right-hand side: 20.9 -> 6.2 ms (the upper triangle's
+// 153 tiles: 53 TFLOP/s of the instruction's 77); 2 x 4-tile tasks per wave, which re-read
+// V from L2 and waited for each slab's loads, were what it took before.
 //
 // The factorisation works on 64 x 64 blocks of the Gram matrix in place: the
 // diagonal block by one wave, its block row by one workgroup per 64 columns

@@ -880,14 +880,18 @@ hipError_t launch_batch_qr(int count, int max_k2, int max_n, int max_nc, const m
 // only the 64-row block holding the diagonal (and the last block of rows) needs
 // conditions, and the blocks without entries are left out; the division by the
 // diagonal is quotient().  m = 512, n = 256: 371 us
-// with one column ahead and every block masked, 203 so, 142 with touch_lines.
+// with one column ahead and every block masked, 203 so, 142 with touch_lines (144 to 153 with
+// quotient()).  The single call's kernel asks for more registers than the 256 it has: 36 are
+// spilled at RPL = 8, 64 at RPL = 16, where there is no more than one column ahead either.  Both
+// are faster all the same: four steps of a 20,000-row solve with m = 1024, n = 256 take 3.3 ms
+// with one column ahead and every block masked, 2.0 so.
 // SKIP0: a reflector with tau = 0 is left out, whatever y holds (0 times an infinite
 // sum would be NaN).
 template <int RPL, bool SKIP0>
 __device__ __forceinline__ void wave_apply_solve(int m, int n, const double *__restrict__ fact,
                                                  const double *__restrict__ tau,
                                                  double (&y)[RPL]) {
-  constexpr int D = RPL <= 8 ? 4 : 1;   // columns ahead (64 % D == 0), as the registers allow
+  constexpr int D = RPL <= 8 ? 4 : 1;   // columns ahead (64 % D == 0)
   const int lane = threadIdx.x & 63;
   int row[RPL];
 #pragma unroll
