@@ -580,12 +580,12 @@ __global__ __launch_bounds__(kBfT) void k_bf_fold_sliced(int64_t d, int k, Cols<
       fb = b;
       cb = values_at(b);
       kb = keys + (int64_t)b * kBfRows;
-  #pragma unroll
+#pragma unroll
       for (int j = 0; j < kSlAhead; ++j) fetch(j);
       bool odd = UNEVEN && __any(word & kBfUneven);   // one of the next four blocks
       if (!odd) {
         put(0, 0);
-  #pragma unroll
+#pragma unroll
         for (int n = 0; n < NS; ++n) {
           cl[n] = lo[0][n];
           ch[n] = hi[0][n];
@@ -595,21 +595,21 @@ __global__ __launch_bounds__(kBfT) void k_bf_fold_sliced(int64_t d, int k, Cols<
       }
       while (b < nblk && !odd) {
         if (UNEVEN) word = tell(b + kSlAhead + q4);
-  #pragma unroll
+#pragma unroll
         for (int j = 0; j < kSlAhead; ++j) {
           if (b >= nblk) break;
           constexpr int kNext[kSlAhead] = {1, 2, 3, 0};
           const int jn = kNext[j], cur = j & 1;
           uint16_t nl[NS], nh[NS];
           put(jn, cur ^ 1);   // (after the last block: a block that is not folded)
-  #pragma unroll
+#pragma unroll
           for (int n = 0; n < NS; ++n) {
             nl[n] = lo[jn][n];
             nh[n] = hi[jn][n];
           }
           fetch(jn);
           fold(stage + cur * kBfRows + (b + 1 < nblk ? 0 : shift), lent + cur * kBfRows);
-  #pragma unroll
+#pragma unroll
           for (int n = 0; n < NS; ++n) {
             cl[n] = nl[n];
             ch[n] = nh[n];
@@ -621,9 +621,9 @@ __global__ __launch_bounds__(kBfT) void k_bf_fold_sliced(int64_t d, int k, Cols<
       }
       if (!UNEVEN || b >= nblk) break;
       // four blocks with an uneven one among them: the sums in LDS (slot: bucket of this part)
-  #pragma unroll
+#pragma unroll
       for (int n = 0; n < NS; ++n)
-  #pragma unroll
+#pragma unroll
         for (int q = 0; q < B; ++q)
           if (s0 + tid + kBfT * n < s1) lacc[(sl[n] - s0) * B + q] = acc[n][q];
       V cv[kV];
@@ -648,24 +648,24 @@ __global__ __launch_bounds__(kBfT) void k_bf_fold_sliced(int64_t d, int k, Cols<
           bf_fold_uneven(sg, lkey, (uint32_t)(s0 * B), (uint32_t)min(s1 * B, k), lacc);
         } else {
           const uint16_t *ends = lent + kBfRows;
-  #pragma unroll 1
+#pragma unroll 1
           for (int s = s0 + tid; s < s1; s += kBfT) {
             T sums[B];
-  #pragma unroll
+#pragma unroll
             for (int q = 0; q < B; ++q) sums[q] = lacc[(s - s0) * B + q];
             walk(reinterpret_cast<const unsigned char *>(sg),
                  reinterpret_cast<const unsigned char *>(lent), s > 0 ? 2u * ends[s - 1] : 0u,
                  2u * ends[s], sums);
-  #pragma unroll
+#pragma unroll
             for (int q = 0; q < B; ++q) lacc[(s - s0) * B + q] = sums[q];
           }
         }
         calm = unb ? 0 : calm + 1;
         __syncthreads();
       }
-  #pragma unroll
+#pragma unroll
       for (int n = 0; n < NS; ++n)
-  #pragma unroll
+#pragma unroll
         for (int q = 0; q < B; ++q) acc[n][q] = lacc[(sl[n] - s0) * B + q];
     }
   };
