@@ -651,7 +651,7 @@ constexpr int64_t kCsSixRows = 393216;
 // set of them at a time, all at the same rows: one group's read of the codes
 // (as many bytes per column as FP32 data) then serves the
 // others, and only the column tiles left over are shared by rows.  HBM reads went
-// from 2.3 to 1.23 times the algorithmic bytes; what bounds it now is data and code
+// from 2.3 to 1.21 times the algorithmic bytes; what bounds it now is data and code
 // of every element going from L2 to one compute unit per bucket tile, 14 TB/s in
 // FP32 (16,777,216 x 129 FP32, k = 32,768: 2.67 -> 2.53 ms by the sets, 2.46 with six
 // vectors in flight for four; 8,388,608 x 65 FP64: 1.17 -> 1.07 ms.  A barrier per
